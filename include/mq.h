@@ -630,12 +630,14 @@ mq_status mq_arl_backward(const float* x, const float* g, int64_t numel, float a
  *              hidden keys hold the probability-0 code), so they may be
  *              skipped; -1: none
  *   workspace  device, 256-byte aligned, >= mq_attn_matmul_workspace_bytes
- *              bytes; overwritten with the per-row zero-point terms, the
- *              per-row sums of B and b_scale (calls that may run
+ *              bytes; may be overwritten with the per-row zero-point terms,
+ *              the per-row sums of B and b_scale (calls that may run
  *              concurrently must not share it)
- *   path       MQ_PATH_AUTO (tiled MFMA kernel for M > 16 when the strides
- *              keep 16-byte aligned rows, else the generic kernel),
- *              MQ_PATH_PREFILL or MQ_PATH_GENERIC
+ *   path       MQ_PATH_AUTO (K <= 128 or N <= 256, the two products of
+ *              attention: one launch at any M, stride and alignment; else
+ *              the tiled kernel for M > 16 when the strides keep 16-byte
+ *              aligned rows), MQ_PATH_PREFILL (the tiled kernel) or
+ *              MQ_PATH_GENERIC; every path computes the same bits
  *   out_causal, in_causal in [-1, 2^40]
  * Errors: MQ_ERR_INVALID_ARG for any violation above.
  */

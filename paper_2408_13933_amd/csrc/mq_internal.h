@@ -145,6 +145,17 @@ hipError_t launch_rmsnorm(const int16_t* x, int64_t M, int64_t K, float ax, int3
 hipError_t launch_softmax(const int16_t* x, int64_t M, int64_t K, float ax, float ay, int32_t zy,
                           int32_t bits, int64_t period, int64_t offset, void* y, hipStream_t st);
 
+// The attention products in one launch at any alignment (see attention.hip).
+// kAttnWideK: the largest K whose sums stay in int32.
+constexpr int kAttnWideK = 128;
+bool attn_direct_supported(int64_t M, int64_t N, int64_t ldy, int32_t H, int32_t G);
+hipError_t launch_attn_direct(const int16_t* a, int64_t lda, int64_t a_hs, int32_t H,
+                              const int8_t* b, int64_t ldb, int64_t b_hs, int32_t G, int64_t M,
+                              int64_t N, int64_t K, float a_scale, int32_t a_zp, float b_scale,
+                              int32_t b_zp, float out_scale, int32_t out_zp, int32_t out_bits,
+                              void* y, int64_t ldy, int64_t y_hs, int64_t out_causal,
+                              int64_t in_causal, hipStream_t s);
+
 hipError_t launch_attn_sums(const int16_t* a, int64_t lda, int64_t a_bs, int32_t H, int64_t M,
                             const int8_t* b, int64_t ldb, int64_t b_bs, int32_t G, int64_t N,
                             int64_t K, int32_t a_zp, int32_t b_zp, float b_scale,

@@ -23,9 +23,10 @@ struct ColParams {
 // accumulator units.  fp64 throughout: the product of two fp32 values is
 // exact in fp64, the division is one correctly rounded operation, and
 // frexp/ldexp/rint are exact, so the integers do not depend on the device.
-__device__ inline ColParams derive_col_params_v(float a_scale, float w_scale, float out_scale,
-                                                bool has_bias, float bias_n, int32_t colsum,
-                                                int32_t a_zp)
+__host__ __device__ inline ColParams derive_col_params_v(float a_scale, float w_scale,
+                                                         float out_scale,
+                                                         bool has_bias, float bias_n,
+                                                         int32_t colsum, int32_t a_zp)
 {
 #pragma clang fp contract(off)
     ColParams p;
@@ -165,7 +166,7 @@ struct EpiInt {
     int32_t m0, rnd, shr, pre, bnd;
 };
 
-__device__ inline EpiInt epi_int_params(const ColParams& cp)
+__host__ __device__ inline EpiInt epi_int_params(const ColParams& cp)
 {
     EpiInt e;
     e.m0 = cp.m0;

@@ -221,6 +221,42 @@ __device__ inline void store8(void* y, int64_t i, const int32_t* q)
     }
 }
 
+// Eight codes at x, any alignment (RAG) or 16-byte aligned; n < 8: only the
+// first n exist and are read, the others come back as zeros.
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ inline int4 load8_any(const int16_t* x, int n)
+{
+    if (n >= 8) {
+        const v4i_any v = *reinterpret_cast<const v4i_any*>(x);
+        return make_int4(v[0], v[1], v[2], v[3]);
+    }
+    int w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int u = 0; u < 7; ++u)
+        if (u < n) w[u / 2] |= (int)((uint32_t)(uint16_t)x[u] << (16 * (u & 1)));
+    return make_int4(w[0], w[1], w[2], w[3]);
+}
+
+// Eight codes to y[i .. i+7] at any alignment, only the first n of them.
+template <int BITS>
+__device__ inline void store8_any(void* y, int64_t i, const int32_t* q, int n)
+{
+    using T = std::conditional_t<BITS == 8, int8_t, int16_t>;
+    T* dst = static_cast<T*>(y) + i;
+    if (n >= 8) {
+        struct __attribute__((packed)) Run {
+            T v[8];
+        } run;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) run.v[u] = (T)q[u];
+        *reinterpret_cast<Run*>(dst) = run;
+    } else {
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+            if (u < n) dst[u] = (T)q[u];
+    }
+}
+
 // Table lookup fused with the product of two dequantized codes: the gated
 // unit SiLU(gate) * up without the SiLU codes going through memory.
 // u = lut[x1 + 32768] (LB-bit entries in format (a1, z1)), then the product
@@ -380,9 +416,8 @@ __device__ inline int64_t causal_keys(int64_t m, int64_t K, int64_t period, int6
     return n < K ? n : K;
 }
 
-// Rows of at most 2048 codes (K % 8 == 0, 16-byte aligned), one wave per
-// row, NC chunks of eight codes per lane (chunk c of lane t holds keys
-// 8 (t + 64 c) .. +7).  The exponent alpha (x_k - max) is -alpha d with
+// Rows of at most 2048 codes, one wave per row, NC chunks of eight codes per
+// lane (chunk c of lane t holds keys 8 (t + 64 c) .. +7).  The exponent alpha (x_k - max) is -alpha d with
 // d = max - x_k an integer in [0, 65535] and alpha an fp32 scale, so
 // alpha d is exact in fp64 and, for d = 256 h + l,
 //   exp(-alpha d) = exp(-256 alpha h) exp(-alpha l).
@@ -476,8 +511,8 @@ __device__ inline int32_t requant_prob(double e, double s, int32_t zy)
     return min(max(r, qmin), qmax);
 }
 
-template <int BITS, bool CLAMP>
-__device__ inline void requant_chunk(const double* e, int k0, int n, double s, int32_t zy,
+template <int BITS, bool CLAMP, bool RAG>
+__device__ inline void requant_chunk(const double* e, int k0, int n, int K, double s, int32_t zy,
                                      void* y, int64_t base)
 {
     int32_t o[8];
@@ -491,51 +526,53 @@ __device__ inline void requant_chunk(const double* e, int k0, int n, double s, i
 #pragma unroll
         for (int u = 0; u < 8; ++u) o[u] = zy;
     }
-    store8<BITS>(y, base + k0, o);
+    if constexpr (RAG) store8_any<BITS>(y, base + k0, o, K - k0);
+    else store8<BITS>(y, base + k0, o);
 }
 
-// one row: m and n (keys visible, 1 <= n <= K <= 512 NC) are wave-uniform
-template <int BITS, int NC>
-__device__ inline void softmax_table_row(int64_t m, int K, int n, const int4* q,
-                                         const double* tab, double ri, int32_t zy,
-                                         void* __restrict__ y)
+// The lane's chunks of one row (chunk c starts at key k0(c)): their largest
+// visible code, the exponentials of all of them and their sum, the codes.
+template <int NC, class K0>
+__device__ inline int32_t chunk_max(const int4* q, int n, K0 k0)
 {
-#pragma clang fp contract(off)
-    const int lane = threadIdx.x & 63;
     int32_t mx = -32768;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const int k0 = 8 * (lane + 64 * c);
         const int4 w = q[c];
-        if (k0 + 8 <= n) {
+        if (k0(c) + 8 <= n) {
             const s16x2 a = __builtin_elementwise_max(as_s16x2(w.x), as_s16x2(w.y));
             const s16x2 b = __builtin_elementwise_max(as_s16x2(w.z), as_s16x2(w.w));
             const s16x2 h = __builtin_elementwise_max(a, b);
             mx = max(mx, max((int32_t)h.x, (int32_t)h.y));
-        } else if (k0 < n) {
+        } else if (k0(c) < n) {
             const int16_t* v = reinterpret_cast<const int16_t*>(&q[c]);
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (k0 + u < n) mx = max(mx, (int32_t)v[u]);
+                if (k0(c) + u < n) mx = max(mx, (int32_t)v[u]);
         }
     }
-    mx = wave_max_i32(mx);
+    return mx;
+}
+
+template <int NC, class K0>
+__device__ inline double chunk_exp(const int4* q, int n, int32_t mx, const double* tab, K0 k0,
+                                   double (&e)[NC][8])
+{
+#pragma clang fp contract(off)
     const s16x2 mx2 = {(short)mx, (short)mx};
-    double e[NC][8];
     double sum = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const int k0 = 8 * (lane + 64 * c);
-        if (k0 < n) {
+        if (k0(c) < n) {
             // hidden keys of a partial chunk read valid entries (their
             // codes are zero or real scores) and are zeroed below
             exp_pair(q[c].x, mx2, tab, e[c][0], e[c][1]);
             exp_pair(q[c].y, mx2, tab, e[c][2], e[c][3]);
             exp_pair(q[c].z, mx2, tab, e[c][4], e[c][5]);
             exp_pair(q[c].w, mx2, tab, e[c][6], e[c][7]);
-            if (k0 + 8 > n) {
+            if (k0(c) + 8 > n) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) e[c][u] = k0 + u < n ? e[c][u] : 0.0;
+                for (int u = 0; u < 8; ++u) e[c][u] = k0(c) + u < n ? e[c][u] : 0.0;
             }
         } else {
 #pragma unroll
@@ -544,35 +581,47 @@ __device__ inline void softmax_table_row(int64_t m, int K, int n, const int4* q,
 #pragma unroll
         for (int u = 0; u < 8; ++u) sum += e[c][u];
     }
-    sum = wave_sum_f64(sum);  // >= 1: the maximum key contributes exp(0)
-    const double s = (1.0 / sum) * ri;
-    const int64_t base = m * K;
+    return sum;
+}
+
+template <int BITS, int NC, bool RAG, class K0>
+__device__ inline void chunk_codes(const double (&e)[NC][8], int n, int K, double sum, double ri,
+                                   int32_t zy, void* y, int64_t base, K0 k0)
+{
+#pragma clang fp contract(off)
+    const double s = (1.0 / sum) * ri;  // sum >= 1: the maximum key contributes exp(0)
     if (s <= 1e9) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const int k0 = 8 * (lane + 64 * c);
-            if (k0 < K) requant_chunk<BITS, false>(e[c], k0, n, s, zy, y, base);
-        }
+        for (int c = 0; c < NC; ++c)
+            if (k0(c) < K) requant_chunk<BITS, false, RAG>(e[c], k0(c), n, K, s, zy, y, base);
     } else {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const int k0 = 8 * (lane + 64 * c);
-            if (k0 < K) requant_chunk<BITS, true>(e[c], k0, n, s, zy, y, base);
-        }
+        for (int c = 0; c < NC; ++c)
+            if (k0(c) < K) requant_chunk<BITS, true, RAG>(e[c], k0(c), n, K, s, zy, y, base);
     }
 }
 
-template <int BITS, int NC>
+// the two factor tables: [0, 256): exp(-256 alpha h); [256, 512): exp(-alpha l)
+__device__ inline void fill_exp_tables(double* tab, double a)
+{
+#pragma clang fp contract(off)
+    for (int i = threadIdx.x; i < 512; i += blockDim.x)
+        tab[i] = i < 256 ? exp(-(a * (double)(256 * i))) : exp(-(a * (double)(i - 256)));
+}
+
+// RAG: rows that are not whole aligned chunks (K % 8 != 0 or an unaligned
+// buffer) through loads and stores of any alignment; the aligned form reads
+// through the row's buffer descriptor, which costs no branch per chunk.
+// 32 x 777 causal rows of 777 codes: 70 us on the strided kernel (an exp per
+// key and pass), 26 us here.
+template <int BITS, int NC, bool RAG>
 __global__ __launch_bounds__(kSmWaves * 64) void softmax_table_kernel(
     const int16_t* __restrict__ x, int64_t M, int64_t K, float ax, float ay, int32_t zy,
     int64_t period, int64_t offset, void* __restrict__ y)
 {
-#pragma clang fp contract(off)
-    __shared__ double tab[512];  // [0, 256): exp(-256 alpha h); [256, 512): exp(-alpha l)
+    __shared__ double tab[512];
     const int t = threadIdx.x, lane = t & 63;
-    const double a = (double)ax;
-    for (int i = t; i < 512; i += kSmWaves * 64)
-        tab[i] = i < 256 ? exp(-(a * (double)(256 * i))) : exp(-(a * (double)(i - 256)));
+    fill_exp_tables(tab, (double)ax);
     const int64_t G = (int64_t)gridDim.x * kSmWaves;
     const int64_t g = (int64_t)blockIdx.x * kSmWaves + __builtin_amdgcn_readfirstlane(t >> 6);
     auto row_of = [&](int r) -> int64_t {
@@ -586,19 +635,29 @@ __global__ __launch_bounds__(kSmWaves * 64) void softmax_table_kernel(
         const int64_t n = r + offset + 1;
         return (int)(n < K ? n : K);
     };
-    // chunks from ceil(n / 8) on lie outside the row's descriptor and read
-    // as zeros without a memory access
+    auto k0 = [&](int c) { return 8 * (lane + 64 * c); };
     int4 q[2][NC];
     int n[2];
     auto load = [&](int slot, int r) {
         const int64_t m = row_of(r);
         n[slot] = keys_of(m);
-        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)(x + (m < M ? m : 0) * K), (short)0, (n[slot] + 7) / 8 * 16, 0x00020000);
+        const int16_t* const row = x + (m < M ? m : 0) * K;
+        if constexpr (RAG) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b128(rx, 16 * (lane + 64 * c), 0, 0);
-            q[slot][c] = make_int4((int)v[0], (int)v[1], (int)v[2], (int)v[3]);
+            for (int c = 0; c < NC; ++c) {
+                q[slot][c] = make_int4(0, 0, 0, 0);
+                if (k0(c) < n[slot]) q[slot][c] = load8_any(row + k0(c), (int)K - k0(c));
+            }
+        } else {
+            // chunks from ceil(n / 8) on lie outside the row's descriptor and
+            // read as zeros without a memory access
+            const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)row, (short)0, (n[slot] + 7) / 8 * 16, 0x00020000);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(rx, 2 * k0(c), 0, 0);
+                q[slot][c] = make_int4((int)v[0], (int)v[1], (int)v[2], (int)v[3]);
+            }
         }
     };
     load(0, 0);
@@ -609,76 +668,52 @@ __global__ __launch_bounds__(kSmWaves * 64) void softmax_table_kernel(
     for (int r = 0; r < kSmRows; ++r) {
         const int slot = r & 1;
         const int64_t m = row_of(r);
-        if (m < M) softmax_table_row<BITS, NC>(m, (int)K, n[slot], q[slot], tab, ri, zy, y);
+        if (m < M) {
+            double e[NC][8];
+            const int32_t mx = wave_max_i32(chunk_max<NC>(q[slot], n[slot], k0));
+            const double sum = wave_sum_f64(chunk_exp<NC>(q[slot], n[slot], mx, tab, k0, e));
+            chunk_codes<BITS, NC, RAG>(e, n[slot], (int)K, sum, ri, zy, y, m * K, k0);
+        }
         if (r + 2 < kSmRows) load(slot, r + 2);
     }
 }
 
-template <int BITS, int NCH>
-__global__ __launch_bounds__(kThreads) void softmax_regs_kernel(const int16_t* __restrict__ x,
-                                                                int64_t K, float ax, float ay,
-                                                                int32_t zy, int64_t period,
-                                                                int64_t offset,
-                                                                void* __restrict__ y)
+// The same with four waves per row and one row per block: rows of up to 8192
+// codes, and few rows (the 32 heads of one query), where a wave per row
+// would leave most of the chip idle and 24 keys in a lane's chain (32 rows of
+// 1531 codes: 8.0 us on the strided kernel, 3.7 us here).
+template <int BITS, int NC>
+__global__ __launch_bounds__(kThreads) void softmax_block_kernel(
+    const int16_t* __restrict__ x, int64_t K, float ax, float ay, int32_t zy, int64_t period,
+    int64_t offset, void* __restrict__ y)
 {
 #pragma clang fp contract(off)
-    __shared__ int32_t red_i[kThreads / 64];
-    __shared__ double red_d[kThreads / 64];
+    constexpr int NW = kThreads / 64;
+    __shared__ double tab[512];
+    __shared__ int32_t red_i[NW];
+    __shared__ double red_d[NW];
     const int64_t m = blockIdx.x;
-    const int64_t n = causal_keys(m, K, period, offset);  // keys this row sees
-    RowRegs<NCH> r;
-    r.load(x + m * K, K);
-    int32_t mx = -32768;
+    const int n = (int)causal_keys(m, K, period, offset);  // keys this row sees
+    const int wave = threadIdx.x >> 6;
+    auto k0 = [&](int c) { return 8 * ((int)threadIdx.x + kThreads * c); };
+    int4 q[NC];
 #pragma unroll
-    for (int c = 0; c < NCH; ++c)
-        if (r.live[c])
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (8 * ((int64_t)threadIdx.x + kThreads * c) + u < n)
-                    mx = max(mx, (int32_t)r.v[c][u]);
-    for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o));
-    if ((threadIdx.x & 63) == 0) red_i[threadIdx.x >> 6] = mx;
+    for (int c = 0; c < NC; ++c) {
+        q[c] = make_int4(0, 0, 0, 0);
+        if (k0(c) < n) q[c] = load8_any(x + m * K + k0(c), (int)K - k0(c));
+    }
+    fill_exp_tables(tab, (double)ax);
+    int32_t mx = wave_max_i32(chunk_max<NC>(q, n, k0));
+    if ((threadIdx.x & 63) == 0) red_i[wave] = mx;
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) mx = max(mx, red_i[w]);
-    const double a = (double)ax;
-    double e[NCH][8];
-    double sum = 0.0;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const int64_t k0 = 8 * ((int64_t)threadIdx.x + kThreads * c);
-        if (r.live[c] && k0 < n) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                e[c][u] = k0 + u < n ? exp(a * (double)((int32_t)r.v[c][u] - mx)) : 0.0;
-                sum += e[c][u];
-            }
-        } else {  // past the causal boundary (or past K): no exponentials
-#pragma unroll
-            for (int u = 0; u < 8; ++u) e[c][u] = 0.0;
-        }
-    }
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if ((threadIdx.x & 63) == 0) red_d[threadIdx.x >> 6] = sum;
+    for (int w = 0; w < NW; ++w) mx = max(mx, red_i[w]);
+    double e[NC][8];
+    double sum = wave_sum_f64(chunk_exp<NC>(q, n, mx, tab, k0, e));
+    if ((threadIdx.x & 63) == 0) red_d[wave] = sum;
     __syncthreads();
-    sum = 0.0;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) sum += red_d[w];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        if (!r.live[c]) continue;
-        const int64_t k0 = 8 * ((int64_t)threadIdx.x + kThreads * c);
-        int32_t q[8];
-        if (k0 < n) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                q[u] = k0 + u < n ? requant_f64<BITS>(e[c][u] / sum, (double)ay, zy) : zy;
-        } else {  // keys past the causal boundary: probability 0, no arithmetic
-#pragma unroll
-            for (int u = 0; u < 8; ++u) q[u] = zy;
-        }
-        store8<BITS>(y, m * K + k0, q);
-    }
+    sum = (red_d[0] + red_d[1]) + (red_d[2] + red_d[3]);
+    chunk_codes<BITS, NC, true>(e, n, (int)K, sum, 1.0 / (double)ay, zy, y, m * K, k0);
 }
 
 // RMSNorm: ss = sum (x - zp_x)^2 (exact, int64); ms = alpha^2 ss / K + eps;
@@ -863,14 +898,6 @@ void rmsnorm_regs(const int16_t* x, int64_t M, int64_t K, float ax, int32_t zx,
                                                                     zy, y);
 }
 
-template <int BITS, int NCH>
-void softmax_regs(const int16_t* x, int64_t M, int64_t K, float ax, float ay, int32_t zy,
-                  int64_t period, int64_t offset, void* y, hipStream_t st)
-{
-    softmax_regs_kernel<BITS, NCH><<<(unsigned)M, kThreads, 0, st>>>(x, K, ax, ay, zy, period,
-                                                                    offset, y);
-}
-
 // register-resident rows: K % 8 == 0, 16-byte aligned x and y, chunks per
 // thread (0: the strided kernel)
 static int row_chunks(const int16_t* x, const void* y, int64_t K)
@@ -930,47 +957,44 @@ hipError_t launch_add_rmsnorm(const int16_t* x1, float a1, int32_t z1, const int
     return launch_rmsnorm(h, M, K, ah, zh, gamma, eps, ay, zy, bits, y, st);
 }
 
-template <int BITS, int NC>
-static void softmax_table(const int16_t* x, int64_t M, int64_t K, float ax, float ay, int32_t zy,
-                          int64_t period, int64_t offset, void* y, hipStream_t st)
+template <int BITS>
+static void softmax_t(const int16_t* x, int64_t M, int64_t K, float ax, float ay, int32_t zy,
+                      int64_t P, int64_t O, void* y, hipStream_t st)
 {
+    // a wave per row when that gives every SIMD one; rows of more than 2048
+    // codes (a block holds 8192) and few rows take a block each
+    if (K > 2048 || (M < 1024 && K > 512)) {
+        const dim3 g((unsigned)M), b(kThreads);
+        if (K <= 2048) softmax_block_kernel<BITS, 1><<<g, b, 0, st>>>(x, K, ax, ay, zy, P, O, y);
+        else if (K <= 4096) softmax_block_kernel<BITS, 2><<<g, b, 0, st>>>(x, K, ax, ay, zy, P, O, y);
+        else softmax_block_kernel<BITS, 4><<<g, b, 0, st>>>(x, K, ax, ay, zy, P, O, y);
+        return;
+    }
     constexpr int RPB = kSmRows * kSmWaves;
-    softmax_table_kernel<BITS, NC><<<(unsigned)((M + RPB - 1) / RPB), kSmWaves * 64, 0, st>>>(
-        x, M, K, ax, ay, zy, period, offset, y);
+    const dim3 g((unsigned)((M + RPB - 1) / RPB)), b(kSmWaves * 64);
+    const bool rag = K % 8 != 0 || ((uintptr_t)x % 16) != 0 || ((uintptr_t)y % 16) != 0;
+    if (rag) {
+        if (K <= 512) softmax_table_kernel<BITS, 1, true><<<g, b, 0, st>>>(x, M, K, ax, ay, zy, P, O, y);
+        else if (K <= 1024) softmax_table_kernel<BITS, 2, true><<<g, b, 0, st>>>(x, M, K, ax, ay, zy, P, O, y);
+        else softmax_table_kernel<BITS, 4, true><<<g, b, 0, st>>>(x, M, K, ax, ay, zy, P, O, y);
+    } else {
+        if (K <= 512) softmax_table_kernel<BITS, 1, false><<<g, b, 0, st>>>(x, M, K, ax, ay, zy, P, O, y);
+        else if (K <= 1024) softmax_table_kernel<BITS, 2, false><<<g, b, 0, st>>>(x, M, K, ax, ay, zy, P, O, y);
+        else softmax_table_kernel<BITS, 4, false><<<g, b, 0, st>>>(x, M, K, ax, ay, zy, P, O, y);
+    }
 }
 
 hipError_t launch_softmax(const int16_t* x, int64_t M, int64_t K, float ax, float ay, int32_t zy,
                           int32_t bits, int64_t period, int64_t offset, void* y, hipStream_t st)
 {
-    const int ch = row_chunks(x, y, K);
-    const int64_t P = period, O = offset;
-    if (ch == 1 && K <= 2048) {  // one wave per row, 8 NC codes per lane
-        const int nc = K <= 512 ? 1 : K <= 1024 ? 2 : 4;
-        if (bits == 8) {
-            if (nc == 1) softmax_table<8, 1>(x, M, K, ax, ay, zy, P, O, y, st);
-            else if (nc == 2) softmax_table<8, 2>(x, M, K, ax, ay, zy, P, O, y, st);
-            else softmax_table<8, 4>(x, M, K, ax, ay, zy, P, O, y, st);
-        } else {
-            if (nc == 1) softmax_table<16, 1>(x, M, K, ax, ay, zy, P, O, y, st);
-            else if (nc == 2) softmax_table<16, 2>(x, M, K, ax, ay, zy, P, O, y, st);
-            else softmax_table<16, 4>(x, M, K, ax, ay, zy, P, O, y, st);
-        }
-        return hipGetLastError();
+    if (K <= 8192) {
+        if (bits == 8) softmax_t<8>(x, M, K, ax, ay, zy, period, offset, y, st);
+        else softmax_t<16>(x, M, K, ax, ay, zy, period, offset, y, st);
+    } else if (bits == 8) {
+        softmax_kernel<8><<<(unsigned)M, kThreads, 0, st>>>(x, K, ax, ay, zy, period, offset, y);
+    } else {
+        softmax_kernel<16><<<(unsigned)M, kThreads, 0, st>>>(x, K, ax, ay, zy, period, offset, y);
     }
-    if (ch > 0) {
-        if (bits == 8) {
-            if (ch == 1) softmax_regs<8, 1>(x, M, K, ax, ay, zy, P, O, y, st);
-            else if (ch == 2) softmax_regs<8, 2>(x, M, K, ax, ay, zy, P, O, y, st);
-            else softmax_regs<8, 4>(x, M, K, ax, ay, zy, P, O, y, st);
-        } else {
-            if (ch == 1) softmax_regs<16, 1>(x, M, K, ax, ay, zy, P, O, y, st);
-            else if (ch == 2) softmax_regs<16, 2>(x, M, K, ax, ay, zy, P, O, y, st);
-            else softmax_regs<16, 4>(x, M, K, ax, ay, zy, P, O, y, st);
-        }
-        return hipGetLastError();
-    }
-    if (bits == 8) softmax_kernel<8><<<(unsigned)M, kThreads, 0, st>>>(x, K, ax, ay, zy, P, O, y);
-    else softmax_kernel<16><<<(unsigned)M, kThreads, 0, st>>>(x, K, ax, ay, zy, P, O, y);
     return hipGetLastError();
 }
 

@@ -149,6 +149,17 @@ def test_softmax_causal_parity(M, K, period, offset):
     (64, 1016, 16, 0.05, None),
     (33, 2048, 8, 1e-3, (33, 2000)),
     (300, 200, 16, 0.0113, (300, 0)),
+    # rows of any length: no whole chunks, a last chunk of one to seven
+    # codes, shorter than one chunk
+    (1500, 777, 16, 3e-4, (777, 0)),
+    (1030, 1025, 8, 3e-4, None),
+    (40, 7, 16, 1e-3, (20, 0)),
+    (1100, 513, 8, 2e-3, (550, 3)),
+    (5, 2047, 16, 1e-3, None),
+    # few long rows (a block each): one, two and four chunks per thread
+    (32, 1531, 16, 1e-4, None),
+    (32, 4095, 16, 1e-4, (32, 4000)),
+    (3, 8191, 8, 2e-4, None),
 ])
 def test_softmax_table_rows(M, K, out_bits, ax, causal):
     import torch

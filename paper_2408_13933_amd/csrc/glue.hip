@@ -25,30 +25,62 @@ inline int grid_for(int64_t items, int per_block, int cap)
     return (int)g;
 }
 
+// The code before its clamp to the output range: rint(t) + zy.  A quotient
+// beyond +-2^17 saturates whatever the zero-point (|zy| <= 2^15), so it is
+// limited there first (NaN: the low end) and adding 1.5 * 2^52 leaves rint(t)
+// (to nearest, ties to even) in the low word: 32-bit integers throughout.
+__device__ inline double limit_quotient(double t)
+{
+    return fmin(fmax(t, -131072.0), 131072.0);
+}
+constexpr double kRintShift = 6755399441055744.0;  // 1.5 * 2^52
+__device__ inline int32_t rint_low(double shifted)
+{
+    return (int32_t)(uint32_t)__double_as_longlong(shifted);
+}
+
+template <int BITS>
+__device__ inline int32_t clamp_code(int32_t q)
+{
+    constexpr int32_t qmin = -(1 << (BITS - 1)), qmax = (1 << (BITS - 1)) - 1;
+    return min(max(q, qmin), qmax);
+}
+
 template <int BITS>
 __device__ inline int32_t requant_f64(double v, double ay, int32_t zy)
 {
 #pragma clang fp contract(off)
-    constexpr int32_t qmin = -(1 << (BITS - 1)), qmax = (1 << (BITS - 1)) - 1;
-    double t = v / ay;
-    if (!(t == t)) t = -1e300;  // NaN -> the low end
-    t = fmin(fmax(t, -1e18), 1e18);
-    const int64_t q = (int64_t)rint(t) + zy;
-    return (int32_t)(q < qmin ? qmin : (q > qmax ? qmax : q));
+    return clamp_code<BITS>(rint_low(limit_quotient(v / ay) + kRintShift) + zy);
 }
 
-// requant_f64 with the division by ay replaced by a product with its
-// reciprocal ri (one extra rounding)
-template <int BITS>
-__device__ inline int32_t requant_mul(double v, double ri, int32_t zy)
+// N codes.  exact(u) is the quotient of code u as the definition evaluates it
+// (its divisions correctly rounded), fast(u) the same quotient through
+// products with reciprocals: a handful of roundings, within 2^-50 of it
+// relatively.  For |t| <= 2^17 that is within 2^-33, so where fast(u) is
+// further than 2^-30 from every
+// half-integer both round to the same integer; a wave with a code nearer
+// than that evaluates exact(u) for all of its codes.  These kernels are
+// bound by the vector ALU at prompt sizes: with the division, 64-bit integer
+// conversions and clamps per code, RMSNorm of 1024 x 2048 took 9.4 us
+// instead of 4.7, with the residual add 10.9 instead of 6.8, the gated
+// product of 1024 x 5632 12.0 instead of 8.3.
+template <int BITS, int N, class Exact, class Fast>
+__device__ inline void requant_codes(int32_t* q, int32_t zy, Exact exact, Fast fast)
 {
 #pragma clang fp contract(off)
-    constexpr int32_t qmin = -(1 << (BITS - 1)), qmax = (1 << (BITS - 1)) - 1;
-    double t = v * ri;
-    if (!(t == t)) t = -1e300;  // NaN -> the low end
-    t = fmin(fmax(t, -1e18), 1e18);
-    const int64_t q = (int64_t)rint(t) + zy;
-    return (int32_t)(q < qmin ? qmin : (q > qmax ? qmax : q));
+    double far = 0.0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const double t = limit_quotient(fast(u));
+        const double r = t + kRintShift;
+        q[u] = clamp_code<BITS>(rint_low(r) + zy);
+        far = fmax(far, fabs(t - (r - kRintShift)));
+    }
+    if (__builtin_expect(__ballot(far > 0.5 - 0x1p-30) != 0, 0)) {
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            q[u] = clamp_code<BITS>(rint_low(limit_quotient(exact(u)) + kRintShift) + zy);
+    }
 }
 
 template <int BITS>
@@ -59,62 +91,61 @@ __device__ inline void store_code(void* y, int64_t i, int32_t v)
 }
 
 // ---------------------------------------------------------------------------
-// Residual add: v = alpha_1 (x1 - zp_1) + alpha_2 (x2 - zp_2), requantized.
-template <int BITS>
-__device__ inline int32_t add_one(int32_t u, int32_t v, float a1, int32_t z1, float a2,
-                                  int32_t z2, float ay, int32_t zy)
+// Residual add: v = alpha_1 (x1 - zp_1) + alpha_2 (x2 - zp_2); the gated
+// unit SiLU(gate) * up: the product of the two dequantized codes (each
+// factor exact in fp64, the product one rounding).  OP 0: sum, 1: product.
+struct Binary {
+    float a1, a2;
+    int32_t z1, z2;
+};
+template <int OP>
+__device__ inline double binary_value(int32_t u, int32_t v, const Binary& p)
 {
 #pragma clang fp contract(off)
-    const double s = (double)a1 * (double)(u - z1) + (double)a2 * (double)(v - z2);
-    return requant_f64<BITS>(s, (double)ay, zy);
+    const double f1 = (double)p.a1 * (double)(u - p.z1);
+    const double f2 = (double)p.a2 * (double)(v - p.z2);
+    return OP == 0 ? f1 + f2 : f1 * f2;
 }
 
-// Product of the two dequantized codes (each factor exact in fp64, the
-// product one rounding): the gated unit SiLU(gate) * up.
-template <int BITS>
-__device__ inline int32_t mul_one(int32_t u, int32_t v, float a1, int32_t z1, float a2,
-                                  int32_t z2, float ay, int32_t zy)
+// N codes of OP, requantized; ri = 1 / ay
+template <int BITS, int OP, int N, class U, class V>
+__device__ inline void binary_codes(int32_t* q, U u, V v, const Binary& p, double ay, double ri,
+                                    int32_t zy)
 {
 #pragma clang fp contract(off)
-    const double f1 = (double)a1 * (double)(u - z1);
-    const double f2 = (double)a2 * (double)(v - z2);
-    return requant_f64<BITS>(f1 * f2, (double)ay, zy);
+    double w[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) w[k] = binary_value<OP>(u(k), v(k), p);
+    requant_codes<BITS, N>(q, zy, [&](int k) { return w[k] / ay; },
+                           [&](int k) { return w[k] * ri; });
 }
 
-template <int BITS, int OP>
-__device__ inline int32_t binary_one(int32_t u, int32_t v, float a1, int32_t z1, float a2,
-                                     int32_t z2, float ay, int32_t zy)
-{
-    if constexpr (OP == 0) return add_one<BITS>(u, v, a1, z1, a2, z2, ay, zy);
-    else return mul_one<BITS>(u, v, a1, z1, a2, z2, ay, zy);
-}
-
-// n4 groups of four codes through 8-byte loads (aligned buffers), the
+// n8 groups of eight codes through 16-byte loads (aligned buffers), the
 // codes [begin, n) one by one
-// OP 0: sum, OP 1: product of the dequantized codes.
+template <int BITS>
+__device__ inline void store8(void* y, int64_t i, const int32_t* q);
+
 template <int BITS, int OP>
 __global__ __launch_bounds__(kThreads) void add_requant_kernel(
-    const int16_t* __restrict__ x1, float a1, int32_t z1, const int16_t* __restrict__ x2,
-    float a2, int32_t z2, int64_t n4, int64_t begin, int64_t n, float ay, int32_t zy,
-    void* __restrict__ y)
+    const int16_t* __restrict__ x1, const int16_t* __restrict__ x2, Binary p, int64_t n8,
+    int64_t begin, int64_t n, float ay, int32_t zy, void* __restrict__ y)
 {
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     const int64_t t0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    for (int64_t i = t0; i < n4; i += stride) {
-        const short4 u = reinterpret_cast<const short4*>(x1)[i];
-        const short4 v = reinterpret_cast<const short4*>(x2)[i];
-        const int32_t r0 = binary_one<BITS, OP>(u.x, v.x, a1, z1, a2, z2, ay, zy);
-        const int32_t r1 = binary_one<BITS, OP>(u.y, v.y, a1, z1, a2, z2, ay, zy);
-        const int32_t r2 = binary_one<BITS, OP>(u.z, v.z, a1, z1, a2, z2, ay, zy);
-        const int32_t r3 = binary_one<BITS, OP>(u.w, v.w, a1, z1, a2, z2, ay, zy);
-        if constexpr (BITS == 8)
-            reinterpret_cast<char4*>(y)[i] = make_char4((char)r0, (char)r1, (char)r2, (char)r3);
-        else
-            reinterpret_cast<short4*>(y)[i] =
-                make_short4((short)r0, (short)r1, (short)r2, (short)r3);
+    const double ri = 1.0 / (double)ay;
+    for (int64_t i = t0; i < n8; i += stride) {
+        const int4 g = reinterpret_cast<const int4*>(x1)[i];
+        const int4 v = reinterpret_cast<const int4*>(x2)[i];
+        const int16_t* gc = reinterpret_cast<const int16_t*>(&g);
+        const int16_t* vc = reinterpret_cast<const int16_t*>(&v);
+        int32_t q[8];
+        binary_codes<BITS, OP, 8>(q, [&](int k) { return (int32_t)gc[k]; },
+                                  [&](int k) { return (int32_t)vc[k]; }, p, (double)ay, ri, zy);
+        store8<BITS>(y, 8 * i, q);
     }
     for (int64_t i = begin + t0; i < n; i += stride)
-        store_code<BITS>(y, i, binary_one<BITS, OP>(x1[i], x2[i], a1, z1, a2, z2, ay, zy));
+        store_code<BITS>(y, i,
+                         requant_f64<BITS>(binary_value<OP>(x1[i], x2[i], p), (double)ay, zy));
 }
 
 // ---------------------------------------------------------------------------
@@ -196,9 +227,6 @@ __device__ inline int64_t block_sum_i64(int64_t v, int64_t* red)
     return t;
 }
 
-// Rows of at most 8 * 256 * NCH codes with K % 8 == 0 and 16-byte aligned
-// rows stay in registers: chunk c of thread t holds codes
-// 8 (t + 256 c) .. +7, read once with a 16-byte load.
 // Eight codes to y[i .. i+7] with one 8-byte (int8) or 16-byte (int16)
 // store; i is a multiple of 8 and y is 16-byte aligned.
 template <int BITS>
@@ -257,45 +285,76 @@ __device__ inline void store8_any(void* y, int64_t i, const int32_t* q, int n)
     }
 }
 
+// The eight int16 codes of one 16-byte load.
+typedef int v4i __attribute__((ext_vector_type(4)));
+__device__ inline void unpack8(const v4i v, int32_t* c)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        c[2 * i] = (int32_t)(int16_t)v[i];
+        c[2 * i + 1] = v[i] >> 16;
+    }
+}
+
 // Table lookup fused with the product of two dequantized codes: the gated
 // unit SiLU(gate) * up without the SiLU codes going through memory.
 // u = lut[x1 + 32768] (LB-bit entries in format (a1, z1)), then the product
-// of mul_one with x2: the same two steps as mq_lut_apply and
-// mq_mul_requant, so the same bits.
-template <int LB, int OB>
+// with x2: the same two steps as mq_lut_apply and mq_mul_requant, so the
+// same bits.  LDS: the table is copied into LDS first, the block's first
+// codes loaded before it; else (fewer codes than the copy would pay for)
+// entries come from memory.
+template <int LB, int OB, bool LDS>
 __global__ __launch_bounds__(kLutThreads) void lut_mul_kernel(
-    const int16_t* __restrict__ x1, const void* __restrict__ lut, float a1, int32_t z1,
-    const int16_t* __restrict__ x2, float a2, int32_t z2, int64_t n8, int64_t begin, int64_t n,
-    float ay, int32_t zy, void* __restrict__ y)
+    const int16_t* __restrict__ x1, const void* __restrict__ lut, const int16_t* __restrict__ x2,
+    Binary p, int64_t n8, int64_t begin, int64_t n, float ay, int32_t zy, void* __restrict__ y)
 {
     using T = typename std::conditional<LB == 8, int8_t, int16_t>::type;
     extern __shared__ __align__(16) int8_t lds_table[];
-    const T* tab = reinterpret_cast<const T*>(lds_table);
-    {
-        const int4* src = static_cast<const int4*>(lut);
-        int4* dst = reinterpret_cast<int4*>(lds_table);
-        constexpr int chunks = 65536 * sizeof(T) / 16;
-        for (int i = threadIdx.x; i < chunks; i += kLutThreads) dst[i] = src[i];
-    }
-    __syncthreads();
+    const T* tab = LDS ? reinterpret_cast<const T*>(lds_table) : static_cast<const T*>(lut);
     const int64_t stride = (int64_t)gridDim.x * kLutThreads;
     const int64_t t0 = (int64_t)blockIdx.x * kLutThreads + threadIdx.x;
-    for (int64_t i = t0; i < n8; i += stride) {
-        const int4 g = reinterpret_cast<const int4*>(x1)[i];
-        const int4 v = reinterpret_cast<const int4*>(x2)[i];
-        const int16_t* gc = reinterpret_cast<const int16_t*>(&g);
-        const int16_t* vc = reinterpret_cast<const int16_t*>(&v);
-        int32_t q[8];
+    v4i g = {0, 0, 0, 0}, v = {0, 0, 0, 0};
+    if (t0 < n8) {
+        g = reinterpret_cast<const v4i*>(x1)[t0];
+        v = reinterpret_cast<const v4i*>(x2)[t0];
+    }
+    if constexpr (LDS) {
+        const v4i* src = static_cast<const v4i*>(lut);
+        v4i* dst = reinterpret_cast<v4i*>(lds_table);
+        constexpr int chunks = 65536 * sizeof(T) / 16 / kLutThreads;
+        v4i c[chunks];
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            q[u] = mul_one<OB>(tab[(int32_t)gc[u] + 32768], vc[u], a1, z1, a2, z2, ay, zy);
+        for (int i = 0; i < chunks; ++i) c[i] = src[threadIdx.x + i * kLutThreads];
+#pragma unroll
+        for (int i = 0; i < chunks; ++i) dst[threadIdx.x + i * kLutThreads] = c[i];
+        __syncthreads();
+    }
+    const double ri = 1.0 / (double)ay;
+    for (int64_t i = t0; i < n8; i += stride) {
+        v4i gn = g, vn = v;  // the next group is on its way during this one
+        if (i + stride < n8) {
+            gn = reinterpret_cast<const v4i*>(x1)[i + stride];
+            vn = reinterpret_cast<const v4i*>(x2)[i + stride];
+        }
+        int32_t gc[8], vc[8], q[8];
+        unpack8(g, gc);
+        unpack8(v, vc);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) gc[k] = tab[gc[k] + 32768];
+        binary_codes<OB, 1, 8>(q, [&](int k) { return gc[k]; }, [&](int k) { return vc[k]; }, p,
+                               (double)ay, ri, zy);
         store8<OB>(y, 8 * i, q);
+        g = gn;
+        v = vn;
     }
     for (int64_t i = begin + t0; i < n; i += stride)
-        store_code<OB>(y, i, mul_one<OB>(tab[(int32_t)x1[i] + 32768], x2[i], a1, z1, a2, z2, ay,
-                                         zy));
+        store_code<OB>(y, i, requant_f64<OB>(binary_value<1>(tab[(int32_t)x1[i] + 32768], x2[i], p),
+                                             (double)ay, zy));
 }
 
+// Rows of at most 8 * 256 * NCH codes with K % 8 == 0 and 16-byte aligned
+// rows stay in registers: chunk c of thread t holds codes
+// 8 (t + 256 c) .. +7, read once with a 16-byte load.
 template <int NCH>
 struct RowRegs {
     int16_t v[NCH][8];
@@ -315,6 +374,52 @@ struct RowRegs {
     }
 };
 
+// The row's chunks normalized: v = a d [* gamma] / rt, code rint(v / ay) + zy,
+// for d = code - zero-point.  gamma is loaded before the reduction (gm).
+template <int NCH>
+struct GammaRegs {
+    float4 lo[NCH], hi[NCH];
+    __device__ void load(const float* gamma, int64_t K)
+    {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int64_t k0 = 8 * ((int64_t)threadIdx.x + kThreads * c);
+            lo[c] = hi[c] = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+            if (gamma && k0 < K) {
+                // gamma need not be 16-byte aligned
+                const float* g = gamma + k0;
+                lo[c] = make_float4(g[0], g[1], g[2], g[3]);
+                hi[c] = make_float4(g[4], g[5], g[6], g[7]);
+            }
+        }
+    }
+    __device__ double at(int c, int u) const
+    {
+        const float4 h = u < 4 ? lo[c] : hi[c];
+        return (double)((u & 3) == 0 ? h.x : (u & 3) == 1 ? h.y : (u & 3) == 2 ? h.z : h.w);
+    }
+};
+
+template <int BITS, class D, class G>
+__device__ inline void norm_codes(int32_t* q, D d, G gamma, double a, double rt, double ay,
+                                  int32_t zy)
+{
+#pragma clang fp contract(off)
+    const double c = (1.0 / rt) * (1.0 / ay) * a;
+    requant_codes<BITS, 8>(
+        q, zy,
+        [&](int u) {
+            double v = a * (double)d(u);
+            v = v * gamma(u);  // (exact without gamma: 1)
+            v = v / rt;
+            return v / ay;
+        },
+        [&](int u) { return (double)d(u) * gamma(u) * c; });
+}
+
+// sum_k (code - zp)^2 of the row: 32-bit squares (|d| <= 65535), 64-bit sums
+__device__ inline uint64_t square(int32_t d) { return (uint64_t)((uint32_t)d * (uint32_t)d); }
+
 template <int BITS, int NCH>
 __global__ __launch_bounds__(kThreads) void rmsnorm_regs_kernel(const int16_t* __restrict__ x,
                                                                 int64_t K, float ax, int32_t zx,
@@ -327,45 +432,39 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_regs_kernel(const int16_t* _
     const int64_t m = blockIdx.x;
     RowRegs<NCH> r;
     r.load(x + m * K, K);
-    int64_t ss = 0;
+    GammaRegs<NCH> gm;
+    gm.load(gamma, K);
+    uint64_t ss = 0;
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
         if (r.live[c])
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t d = (int64_t)r.v[c][u] - zx;
-                ss += d * d;
-            }
-    ss = block_sum_i64(ss, red);
+            for (int u = 0; u < 8; ++u) ss += square(r.v[c][u] - zx);
+    ss = (uint64_t)block_sum_i64((int64_t)ss, red);
     const double a = (double)ax;
-    const double ms = a * a * (double)ss / (double)K + (double)eps;
+    const double ms = a * a * (double)(int64_t)ss / (double)K + (double)eps;
     const double rt = sqrt(ms);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         if (!r.live[c]) continue;
         const int64_t k0 = 8 * ((int64_t)threadIdx.x + kThreads * c);
         int32_t q[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            double v = a * (double)((int64_t)r.v[c][u] - zx);
-            if (gamma) v = v * (double)gamma[k0 + u];
-            v = v / rt;
-            q[u] = requant_f64<BITS>(v, (double)ay, zy);
-        }
+        norm_codes<BITS>(q, [&](int u) { return r.v[c][u] - zx; },
+                         [&](int u) { return gm.at(c, u); }, a, rt, (double)ay, zy);
         store8<BITS>(y, m * K + k0, q);
     }
 }
 
 // Residual add fused with the RMSNorm that reads its result: per row, the
-// sum codes h = code_h(a1 (x1 - z1) + a2 (x2 - z2)) (add_one) are written
-// and, still in registers, normalized as rmsnorm_regs_kernel normalizes its
-// input.  The same operations as mq_add_requant then mq_rmsnorm, so the
-// same bits, with one read of h less and one launch less.
+// sum codes h = code_h(a1 (x1 - z1) + a2 (x2 - z2)) are written and, still
+// in registers, normalized as rmsnorm_regs_kernel normalizes its input.  The
+// same values as mq_add_requant then mq_rmsnorm, so the same bits, with one
+// read of h less and one launch less.
 template <int BITS, int NCH>
 __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(
-    const int16_t* __restrict__ x1, float a1, int32_t z1, const int16_t* __restrict__ x2,
-    float a2, int32_t z2, int64_t K, float ah, int32_t zh, int16_t* __restrict__ h,
-    const float* __restrict__ gamma, float eps, float ay, int32_t zy, void* __restrict__ y)
+    const int16_t* __restrict__ x1, const int16_t* __restrict__ x2, Binary p, int64_t K, float ah,
+    int32_t zh, int16_t* __restrict__ h, const float* __restrict__ gamma, float eps, float ay,
+    int32_t zy, void* __restrict__ y)
 {
 #pragma clang fp contract(off)
     __shared__ int64_t red[kThreads / 64];
@@ -373,36 +472,32 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(
     RowRegs<NCH> r1, r2;
     r1.load(x1 + m * K, K);
     r2.load(x2 + m * K, K);
+    GammaRegs<NCH> gm;
+    gm.load(gamma, K);
+    const double rih = 1.0 / (double)ah;
     int32_t hc[NCH][8];
-    int64_t ss = 0;
+    uint64_t ss = 0;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         if (!r1.live[c]) continue;
         const int64_t k0 = 8 * ((int64_t)threadIdx.x + kThreads * c);
+        binary_codes<16, 0, 8>(hc[c], [&](int u) { return (int32_t)r1.v[c][u]; },
+                               [&](int u) { return (int32_t)r2.v[c][u]; }, p, (double)ah, rih, zh);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            hc[c][u] = add_one<16>(r1.v[c][u], r2.v[c][u], a1, z1, a2, z2, ah, zh);
-            const int64_t d = (int64_t)hc[c][u] - zh;
-            ss += d * d;
-        }
+        for (int u = 0; u < 8; ++u) ss += square(hc[c][u] - zh);
         store8<16>(h, m * K + k0, hc[c]);
     }
-    ss = block_sum_i64(ss, red);
+    ss = (uint64_t)block_sum_i64((int64_t)ss, red);
     const double a = (double)ah;
-    const double ms = a * a * (double)ss / (double)K + (double)eps;
+    const double ms = a * a * (double)(int64_t)ss / (double)K + (double)eps;
     const double rt = sqrt(ms);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         if (!r1.live[c]) continue;
         const int64_t k0 = 8 * ((int64_t)threadIdx.x + kThreads * c);
         int32_t q[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            double v = a * (double)((int64_t)hc[c][u] - zh);
-            if (gamma) v = v * (double)gamma[k0 + u];
-            v = v / rt;
-            q[u] = requant_f64<BITS>(v, (double)ay, zy);
-        }
+        norm_codes<BITS>(q, [&](int u) { return hc[c][u] - zh; },
+                         [&](int u) { return gm.at(c, u); }, a, rt, (double)ay, zy);
         store8<BITS>(y, m * K + k0, q);
     }
 }
@@ -793,17 +888,16 @@ static hipError_t launch_binary(const int16_t* x1, float a1, int32_t z1, const i
                                 float a2, int32_t z2, int64_t n, float ay, int32_t zy,
                                 int32_t bits, void* y, hipStream_t st)
 {
-    const uintptr_t ya = bits == 8 ? 4 : 8;
-    const bool vec = ((uintptr_t)x1 % 8) == 0 && ((uintptr_t)x2 % 8) == 0 &&
+    const uintptr_t ya = bits == 8 ? 8 : 16;
+    const bool vec = ((uintptr_t)x1 % 16) == 0 && ((uintptr_t)x2 % 16) == 0 &&
                      ((uintptr_t)y % ya) == 0;
-    const int64_t n4 = vec ? n / 4 : 0;
-    const int g = grid_for(vec ? n4 : n, kThreads * 2, 256 * 64);
+    const int64_t n8 = vec ? n / 8 : 0;
+    const int g = grid_for(vec ? n8 : n, kThreads, 256 * 64);
+    const Binary p{a1, a2, z1, z2};
     if (bits == 8)
-        add_requant_kernel<8, OP><<<g, kThreads, 0, st>>>(x1, a1, z1, x2, a2, z2, n4, n4 * 4, n,
-                                                          ay, zy, y);
+        add_requant_kernel<8, OP><<<g, kThreads, 0, st>>>(x1, x2, p, n8, n8 * 8, n, ay, zy, y);
     else
-        add_requant_kernel<16, OP><<<g, kThreads, 0, st>>>(x1, a1, z1, x2, a2, z2, n4, n4 * 4, n,
-                                                           ay, zy, y);
+        add_requant_kernel<16, OP><<<g, kThreads, 0, st>>>(x1, x2, p, n8, n8 * 8, n, ay, zy, y);
     return hipGetLastError();
 }
 
@@ -867,14 +961,23 @@ static hipError_t lut_mul_launch(const int16_t* x1, const void* lut, float a1, i
     const bool vec = ((uintptr_t)x1 % 16) == 0 && ((uintptr_t)x2 % 16) == 0 &&
                      ((uintptr_t)y % ya) == 0 && ((uintptr_t)lut % 16) == 0;
     const int64_t n8 = vec ? n / 8 : 0;
+    const Binary p{a1, a2, z1, z2};
+    // up to 64 Ki codes (the gated unit of a few tokens) cost less from
+    // memory than the copy of the table
+    if (n <= 65536) {
+        const int g = grid_for(vec ? n8 : n, kLutThreads, 256 * 64);
+        lut_mul_kernel<LB, OB, false><<<g, kLutThreads, 0, st>>>(x1, lut, x2, p, n8, n8 * 8, n, ay,
+                                                                 zy, y);
+        return hipGetLastError();
+    }
     const int g = grid_for(n, kLutThreads * 16, LB == 8 ? 512 : 256);
     const size_t lds = 65536 * (LB / 8);
     static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&lut_mul_kernel<LB, OB>),
+        reinterpret_cast<const void*>(&lut_mul_kernel<LB, OB, true>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr != hipSuccess) return attr;
-    lut_mul_kernel<LB, OB><<<g, kLutThreads, lds, st>>>(x1, lut, a1, z1, x2, a2, z2, n8, n8 * 8,
-                                                       n, ay, zy, y);
+    lut_mul_kernel<LB, OB, true><<<g, kLutThreads, lds, st>>>(x1, lut, x2, p, n8, n8 * 8, n, ay, zy,
+                                                              y);
     return hipGetLastError();
 }
 
@@ -940,14 +1043,15 @@ hipError_t launch_add_rmsnorm(const int16_t* x1, float a1, int32_t z1, const int
     const int ch = row_chunks(x1, y, K);
     if (ch > 0 && row_chunks(x2, h, K) > 0) {
         const dim3 g((unsigned)M), b(kThreads);
+        const Binary p{a1, a2, z1, z2};
         if (bits == 8) {
-            if (ch == 1) add_rmsnorm_kernel<8, 1><<<g, b, 0, st>>>(x1, a1, z1, x2, a2, z2, K, ah, zh, h, gamma, eps, ay, zy, y);
-            else if (ch == 2) add_rmsnorm_kernel<8, 2><<<g, b, 0, st>>>(x1, a1, z1, x2, a2, z2, K, ah, zh, h, gamma, eps, ay, zy, y);
-            else add_rmsnorm_kernel<8, 4><<<g, b, 0, st>>>(x1, a1, z1, x2, a2, z2, K, ah, zh, h, gamma, eps, ay, zy, y);
+            if (ch == 1) add_rmsnorm_kernel<8, 1><<<g, b, 0, st>>>(x1, x2, p, K, ah, zh, h, gamma, eps, ay, zy, y);
+            else if (ch == 2) add_rmsnorm_kernel<8, 2><<<g, b, 0, st>>>(x1, x2, p, K, ah, zh, h, gamma, eps, ay, zy, y);
+            else add_rmsnorm_kernel<8, 4><<<g, b, 0, st>>>(x1, x2, p, K, ah, zh, h, gamma, eps, ay, zy, y);
         } else {
-            if (ch == 1) add_rmsnorm_kernel<16, 1><<<g, b, 0, st>>>(x1, a1, z1, x2, a2, z2, K, ah, zh, h, gamma, eps, ay, zy, y);
-            else if (ch == 2) add_rmsnorm_kernel<16, 2><<<g, b, 0, st>>>(x1, a1, z1, x2, a2, z2, K, ah, zh, h, gamma, eps, ay, zy, y);
-            else add_rmsnorm_kernel<16, 4><<<g, b, 0, st>>>(x1, a1, z1, x2, a2, z2, K, ah, zh, h, gamma, eps, ay, zy, y);
+            if (ch == 1) add_rmsnorm_kernel<16, 1><<<g, b, 0, st>>>(x1, x2, p, K, ah, zh, h, gamma, eps, ay, zy, y);
+            else if (ch == 2) add_rmsnorm_kernel<16, 2><<<g, b, 0, st>>>(x1, x2, p, K, ah, zh, h, gamma, eps, ay, zy, y);
+            else add_rmsnorm_kernel<16, 4><<<g, b, 0, st>>>(x1, x2, p, K, ah, zh, h, gamma, eps, ay, zy, y);
         }
         return hipGetLastError();
     }
@@ -1034,13 +1138,18 @@ __global__ __launch_bounds__(256) void rope_kernel(const int16_t* __restrict__ x
     const int32_t q = (int32_t)blockIdx.x * 256 + (int32_t)threadIdx.x;
     if (q >= H * half) return;
     const int32_t h = q / half, i = q - h * half;
+    const double ri = 1.0 / (double)ay;
     for (int64_t t = blockIdx.y; t < T; t += gridDim.y) {
         const int64_t j0 = (t * H + h) * (int64_t)(2 * half) + i, j1 = j0 + half;
         const double c = cs[2 * (t * half + i)], sn = cs[2 * (t * half + i) + 1];
         const double u = (double)ax * (double)((int32_t)x[j0] - zx);
         const double w = (double)ax * (double)((int32_t)x[j1] - zx);
-        store_code<BITS>(y, j0, requant_f64<BITS>(u * c - w * sn, (double)ay, zy));
-        store_code<BITS>(y, j1, requant_f64<BITS>(w * c + u * sn, (double)ay, zy));
+        const double v[2] = {u * c - w * sn, w * c + u * sn};
+        int32_t r[2];
+        requant_codes<BITS, 2>(r, zy, [&](int k) { return v[k] / (double)ay; },
+                               [&](int k) { return v[k] * ri; });
+        store_code<BITS>(y, j0, r[0]);
+        store_code<BITS>(y, j1, r[1]);
     }
 }
 

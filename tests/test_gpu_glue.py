@@ -288,3 +288,58 @@ def test_rope_parity(T, H, D, pos0, out_bits):
     y = mq.mq_rope(_dev(x), H, ax, zx, ay, zy, out_bits, pos0=pos0).cpu().numpy()
     ref = oracle.rope(x, H, ax, zx, ay, zy, out_bits, pos0=pos0)
     _equal_but_ties(y, ref, _rope_pre(x, H, ax, zx, ay, pos0))
+
+
+# The requant of the glue rounds a product with a reciprocal where that is far
+# from every half-integer and evaluates the division otherwise; dyadic scales
+# put half of all sums and products exactly on a tie, tiny and huge scales
+# saturate both ways, and a zero row divides 0 by 0.
+@pytest.mark.parametrize("a1,a2,ay,zy", [(1.0, 1.0, 2.0, -32768), (0.5, 0.25, 0.5, 3),
+                                         (1.0, 3.0, 1e-30, 7), (1e-20, 1e-20, 1e20, -5),
+                                         (3e38, 3e38, 1e-45, 0), (0.1, 0.3, 0.7, 32767)])
+@pytest.mark.parametrize("out_bits", [16, 8])
+def test_glue_requant_ties_and_ends(a1, a2, ay, zy, out_bits):
+    mq = _mq()
+    rng = np.random.default_rng(11)
+    zy = int(np.clip(zy, -(1 << (out_bits - 1)), (1 << (out_bits - 1)) - 1))
+    x1 = rng.integers(-32768, 32768, 8 * 1029 + 3).astype(np.int16)
+    x2 = rng.integers(-32768, 32768, x1.size).astype(np.int16)
+    x1[:64], x2[:64] = 5, 9                       # both at their zero-points
+    x1[64:200] = rng.integers(-60, 60, 136)       # sums inside the int8 grid
+    x2[64:200] = rng.integers(-60, 60, 136)
+    for gpu, ref in ((mq.mq_add_requant, oracle.add_requant),
+                     (mq.mq_mul_requant, oracle.mul_requant)):
+        y = gpu(_dev(x1), a1, 5, _dev(x2), a2, 9, ay, zy, out_bits).cpu().numpy()
+        assert np.array_equal(y, ref(x1, a1, 5, x2, a2, 9, ay, zy, out_bits))
+
+
+@pytest.mark.parametrize("eps,ay", [(0.0, 0.5), (1e-5, 1e-45), (0.0, 3e38)])
+@pytest.mark.parametrize("K", [2048, 4104, 8192])
+def test_rmsnorm_ties_and_ends(K, eps, ay):
+    """Rows of one magnitude (every output +-1, a tie of ay = 2), zero rows
+    without eps (0 / 0: the low end), saturating scales, gains of 0 and of
+    both signs."""
+    mq = _mq()
+    rng = np.random.default_rng(K)
+    x = rng.integers(-32768, 32768, (6, K)).astype(np.int16)
+    x[0] = np.where(rng.random(K) < 0.5, 107, -93)
+    x[1] = 7
+    g = rng.uniform(-2.0, 2.0, K).astype(np.float32)
+    g[::5] = 0.0
+    g[1::5] = 0.25
+    for gamma in (None, g):
+        y = mq.mq_rmsnorm(_dev(x), 0.013, 7, None if gamma is None else _dev(gamma), eps, ay, 0,
+                          16).cpu().numpy()
+        assert np.array_equal(y, oracle.rmsnorm(x, 0.013, 7, gamma, eps, ay, 0, 16))
+
+
+@pytest.mark.parametrize("n", [1, 65536, 65536 + 13, 300000])
+def test_lut_mul_table_in_memory_and_in_lds(n):
+    mq = _mq()
+    rng = np.random.default_rng(n)
+    x1 = rng.integers(-32768, 32768, n).astype(np.int16)
+    x2 = rng.integers(-32768, 32768, n).astype(np.int16)
+    lut = rng.integers(-32768, 32768, 65536).astype(np.int16)
+    ref = oracle.mul_requant(lut[x1.astype(np.int64) + 32768], 9e-5, -3, x2, 1.6e-4, 7, 0.067, 3, 8)
+    y = mq.mq_lut_mul(_dev(x1), _dev(lut), 9e-5, -3, _dev(x2), 1.6e-4, 7, 0.067, 3, 8)
+    assert np.array_equal(y.cpu().numpy(), ref)

@@ -680,22 +680,40 @@ __global__ __launch_bounds__(256) void attn_sums_kernel(const int16_t* a, int64_
         colsum[row - rows_a] = (int32_t)s;  // |s| <= 128 K <= 2^23
 }
 
-// y[c][r] = x[r][c] through a 64 x 64 LDS tile (row pitch 65 bytes keeps
-// the column reads on distinct banks).
+// y[c][r] = x[r][c] through a 64 x 64 LDS tile: one 16-byte load and one
+// 16-byte store per thread at any alignment (edges of the matrix by
+// element).  Bound by latency at the sizes of a value matrix: 1024 x 256
+// took 5.0 us with sixteen one-byte loads and stores per thread one after
+// the other, 2.4 us this way.
 __global__ __launch_bounds__(256) void transpose_i8_kernel(const int8_t* x, int64_t rows,
                                                            int64_t cols, int64_t ldx, int8_t* y)
 {
-    __shared__ int8_t t[64][65];
+    __shared__ int8_t t[64][68];  // t[c][r]
     const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int i = ty; i < 64; i += 4) {
-        const int64_t r = r0 + i, c = c0 + tx;
-        t[i][tx] = (r < rows && c < cols) ? x[r * ldx + c] : 0;
+    const int row = threadIdx.x >> 2, q = (threadIdx.x & 3) * 16;
+    {
+        const int64_t r = r0 + row, c = c0 + q;
+        v4i v = {0, 0, 0, 0};
+        if (r < rows && c < cols) {
+            // the row from one tile before this one on: 32-bit offsets
+            const int64_t w0 = c0 >= 64 ? c0 - 64 : 0;
+            const int64_t left = cols - w0 < 192 ? cols - w0 : 192;
+            v = load16_tail(x + r * ldx + w0, (int32_t)(c - w0), (int32_t)left);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) t[q + i][row] = (int8_t)(v[i / 4] >> (8 * (i % 4)));
     }
     __syncthreads();
-    for (int i = ty; i < 64; i += 4) {
-        const int64_t c = c0 + i, r = r0 + tx;
-        if (c < cols && r < rows) y[c * rows + r] = t[tx][i];
+    const int64_t c = c0 + row, r = r0 + q;
+    if (c >= cols || r >= rows) return;
+    int8_t* dst = y + c * rows + r;
+    v4i v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const int*>(&t[row][q + 4 * i]);
+    if (r + 16 <= rows) {
+        *reinterpret_cast<v4i_u*>(dst) = v;
+    } else {
+        for (int i = 0; i < 16 && r + i < rows; ++i) dst[i] = t[row][q + i];
     }
 }
 

@@ -83,3 +83,15 @@ def test_direct_causal(H, G, T, past):
     prm = (1.0 / 65535, -32768, 0.03, 11, 0.5, 3, 8)
     got = mq.mq_attn_matmul(gp, gv, *prm, in_causal=past).cpu().numpy()
     assert np.array_equal(got, oracle.attn_matmul(p, v, *prm))
+
+
+@pytest.mark.parametrize("rows,cols,ldx", [(15, 15, 15), (64, 64, 64), (65, 127, 131),
+                                           (777, 256, 256), (128, 1, 3), (5, 200, 201)])
+def test_transpose_edges(rows, cols, ldx):
+    """Whole and partial 64 x 64 tiles, rows shorter than one load, rows that
+    start at any byte."""
+    import paper_2408_13933_amd as mq
+    import torch
+    x = np.random.default_rng(rows + cols).integers(-128, 128, (rows, ldx)).astype(np.int8)
+    y = mq.mq_transpose_i8(torch.from_numpy(x).cuda()[:, :cols])
+    assert np.array_equal(y.cpu().numpy(), x[:, :cols].T)

@@ -165,31 +165,45 @@ def _check(status: int, where: str):
 
 # --------------------------------------------------------------------------
 # marshalling helpers (torch is only device memory and streams here)
+# Small calls (a linear over one token runs 4 us on the GPU) are bound by what
+# happens here, so pointers stay plain ints (the declared argument types take
+# them), torch is looked up once, and the current stream's handle is read
+# without building a Stream object (5 of 14 us per call).
+_torch_mod = None
+_get_device = _get_raw_stream = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_mod, _get_device, _get_raw_stream
+    if _torch_mod is None:
+        import torch
+        _get_device = getattr(torch._C, "_cuda_getDevice", None)
+        _get_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _torch_mod = torch
+    return _torch_mod
 
 
 def _dev_ptr(t, dtype, name, shape=None):
-    torch = _torch()
     if t is None:
         raise ValueError(f"{name} is required")
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, (_torch_mod or _torch()).Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream_ptr(stream):
-    torch = _torch()
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _torch_mod or _torch()
+    if _get_device is not None and _get_raw_stream is not None and torch.cuda.is_initialized():
+        return _get_raw_stream(_get_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _act_dtype(bits):
@@ -335,7 +349,7 @@ def _workspace_args(workspace):
     if workspace.dtype != torch.uint8 or workspace.device.type != "cuda" or \
             not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous uint8 device tensor")
-    return ctypes.c_void_p(workspace.data_ptr()), int(workspace.numel())
+    return workspace.data_ptr(), int(workspace.numel())
 
 
 def mq_qlinear_asym(a_q, a_rowsum, w_q, w_bits: int, w_scale, w_zp, w_colsum, a_scale: float,
@@ -693,7 +707,7 @@ def _strided3(t, dtype, name, shape=None):
     bs, rs = t.stride(0), t.stride(1)
     if t.shape[1] <= 1:
         rs = max(rs, t.shape[2])
-    return ctypes.c_void_p(t.data_ptr()), int(bs), int(rs)
+    return t.data_ptr(), int(bs), int(rs)
 
 
 def mq_attn_matmul_workspace_bytes(H: int, G: int, M: int, N: int) -> int:
@@ -743,7 +757,7 @@ def mq_transpose_i8(x, out=None, stream=None):
         raise ValueError("x must have contiguous rows")
     ldx = max(int(x.stride(0)), cols)
     out = torch.empty((cols, rows), dtype=torch.int8, device=x.device) if out is None else out
-    _check(lib().mq_transpose_i8(ctypes.c_void_p(x.data_ptr()), rows, cols, ldx,
+    _check(lib().mq_transpose_i8(x.data_ptr(), rows, cols, ldx,
                                  _dev_ptr(out, torch.int8, "out", (cols, rows)),
                                  _stream_ptr(stream)), "mq_transpose_i8")
     return out
@@ -820,7 +834,7 @@ def mq_probe_read(buf, blocks: int, waves: int, unroll: int = 8, sink=None, stre
         raise ValueError("buf must be a contiguous GPU tensor")
     sink = (torch.empty(blocks * waves, dtype=torch.int32, device=buf.device)
             if sink is None else sink)
-    _check(lib().mq_probe_read(ctypes.c_void_p(buf.data_ptr()),
+    _check(lib().mq_probe_read(buf.data_ptr(),
                                buf.numel() * buf.element_size(), int(blocks), int(waves),
                                int(unroll), _dev_ptr(sink, torch.int32, "sink",
                                                      (blocks * waves,)),

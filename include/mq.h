@@ -373,7 +373,8 @@ typedef struct mq_qlinear_out {
  * prefill path (M > 16 with MQ_PATH_AUTO) with K % 16 == 0 (int8) or
  * K % 32 == 0 (int4) and 16-byte-aligned buffers, one launch takes the
  * output tiles of all the linears, so a set of small layers fills the chip
- * as one large one would; otherwise each linear runs on the path
+ * as one large one would; so it does on the decode path, where a small
+ * layer is mostly latency; otherwise each linear runs on the path
  * mq_qlinear_ex would take with the same path argument.  No K split.
  *   a_q       device int8 [M][K]   a_rowsum  device int32 [M] or NULL (as
  *             for mq_qlinear_asym)

@@ -548,15 +548,18 @@ mq_status mq_qlinear_group(const int8_t* a_q, const int32_t* a_rowsum, int64_t M
     }
     const hipStream_t s = as_stream(stream);
     // the linears with work; one launch when each of them would take the
-    // prefill kernel on its own
+    // prefill kernel on its own, or each the decode kernel (with one token:
+    // each the GEMV, or none)
     mq::GroupArgs g{};
     int first = -1;
-    bool one_launch = true;
+    bool one_launch = true, one_decode = true;
     for (int i = 0; i < n_outs; ++i) {
         const mq::QLinearArgs& p = ps[i];
         if (p.M == 0 || p.N == 0) continue;
         if (first < 0) first = i;
         one_launch = one_launch && resolved[i] == MQ_PATH_PREFILL && mq::prefill_supported(p);
+        one_decode = one_decode && resolved[i] == MQ_PATH_DECODE && mq::decode_supported(p) &&
+                     mq::gemv_supported(p) == mq::gemv_supported(ps[first]);
         mq::GroupPart& gp = g.part[g.n++];
         gp.w = p.w;
         gp.w_scale = p.w_scale;
@@ -570,6 +573,7 @@ mq_status mq_qlinear_group(const int8_t* a_q, const int32_t* a_rowsum, int64_t M
     }
     if (g.n == 0) return MQ_OK;
     if (one_launch && g.n > 1) return from_hip(mq::launch_qlinear_prefill_group(ps[first], g, s));
+    if (one_decode && g.n > 1) return from_hip(mq::launch_qlinear_decode_group(ps[first], g, s));
     for (int i = 0; i < n_outs; ++i) {
         const mq_status st = mq::qlinear_dispatch(ps[i], resolved[i], s);
         if (st != MQ_OK) return st;

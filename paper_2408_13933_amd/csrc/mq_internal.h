@@ -82,6 +82,28 @@ struct GroupArgs {
     int32_t n;
 };
 
+// The linear whose output tiles hold tile `tile` (block-uniform): p takes its
+// weights, per-channel inputs, output and requant constants; returns the tile
+// within the linear.
+__device__ inline int32_t take_group_part(QLinearArgs& p, const GroupArgs& g, int32_t tile)
+{
+    int k = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxGroup; ++i)
+        if (i < g.n && tile >= g.part[i].tile0) k = i;
+    const GroupPart& gp = g.part[k];
+    p.w = gp.w;
+    p.w_scale = gp.w_scale;
+    p.colsum = gp.colsum;
+    p.bias = gp.bias;
+    p.w_zp = gp.w_zp;
+    p.y = gp.y;
+    p.N = gp.N;
+    p.out_scale = gp.out_scale;
+    p.out_zp = gp.out_zp;
+    return tile - gp.tile0;
+}
+
 // Dense defaults of the stride fields.
 __host__ __device__ inline int64_t eff_lda(const QLinearArgs& p) { return p.lda ? p.lda : p.K; }
 __host__ __device__ inline int64_t eff_ldw(const QLinearArgs& p) { return p.ldw ? p.ldw : p.K; }
@@ -174,6 +196,24 @@ hipError_t launch_qlinear_decode(const QLinearArgs& p, hipStream_t s);
 // one token (M = 1, 8-bit codes): the vector-ALU GEMV the decode path takes
 hipError_t launch_qlinear_gemv(const QLinearArgs& p, hipStream_t s);
 bool gemv_supported(const QLinearArgs& p);
+// the linears of g on p's input in one launch (every part meeting
+// decode_supported; with one token all or none of them gemv_supported)
+hipError_t launch_qlinear_decode_group(const QLinearArgs& p, GroupArgs g, hipStream_t s);
+hipError_t launch_qlinear_gemv_group(const QLinearArgs& p, GroupArgs g, hipStream_t s);
+// tile0 and tiles_n of every part for tiles of `channels`; the total, or -1
+// past 2^31
+inline int64_t set_group_tiles(GroupArgs& g, int64_t channels)
+{
+    int64_t t = 0;
+    for (int i = 0; i < g.n; ++i) {
+        g.part[i].tile0 = (int32_t)t;
+        const int64_t n = (g.part[i].N + channels - 1) / channels;
+        g.part[i].tiles_n = (int32_t)n;
+        t += n;
+        if (t > 0x7FFFFFFF) return -1;
+    }
+    return t;
+}
 hipError_t launch_qlinear_prefill(const QLinearArgs& p, hipStream_t s);
 // the linears of g on p's input (8-bit codes, dense, every part meeting
 // prefill_supported), one launch, no K split

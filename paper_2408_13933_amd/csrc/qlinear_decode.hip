@@ -43,7 +43,7 @@ __device__ inline v4i unpack_int4_x16(uint32_t x0, uint32_t x1)
 // MFMAs on its high and offset-low byte planes (split_a16), combined
 // exactly in int64 in the epilogue.
 template <int WBITS, int OBITS, int NWAVES, int R, bool ASYM, bool A16>
-__global__ __launch_bounds__(NWAVES * 64) void qlinear_decode_kernel(QLinearArgs p)
+__device__ __forceinline__ void decode_body(const QLinearArgs& p, int64_t tile)
 {
     constexpr int U = 8;  // 64-wide k steps per load round (one round covers most layers)
     constexpr int32_t qmin = -(1 << (OBITS - 1));
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(NWAVES * 64) void qlinear_decode_kernel(QLinearArgs
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar loop
     const int r16 = lane & 15;  // weight row in the group / token row
     const int kg = lane >> 4;   // 16-wide k group inside a 64-wide step
-    const int64_t n0 = (int64_t)blockIdx.x * R;
+    const int64_t n0 = tile * R;
     // Buffer descriptors over this block's weight rows and the M token rows:
     // a load past a valid row (channel >= N, token >= M, k >= K, or a step
     // beyond this wave's range) returns zeros without touching memory, so
@@ -248,10 +248,39 @@ __global__ __launch_bounds__(NWAVES * 64) void qlinear_decode_kernel(QLinearArgs
     }
 }
 
-template <int WBITS, int OBITS, int R, bool ASYM, bool A16>
-hipError_t launch_r(const QLinearArgs& p, hipStream_t s)
+template <int WBITS, int OBITS, int NWAVES, int R, bool ASYM, bool A16>
+__global__ __launch_bounds__(NWAVES * 64) void qlinear_decode_kernel(QLinearArgs p)
 {
-    const int64_t blocks = (p.N + R - 1) / R;
+    decode_body<WBITS, OBITS, NWAVES, R, ASYM, A16>(p, blockIdx.x);
+}
+
+// several linears on one input, 8-bit codes
+template <int WBITS, int OBITS, int NWAVES, int R, bool ASYM>
+__global__ __launch_bounds__(NWAVES * 64) void qlinear_decode_group_kernel(QLinearArgs p,
+                                                                           GroupArgs g)
+{
+    const int32_t tile = take_group_part(p, g, (int32_t)blockIdx.x);
+    decode_body<WBITS, OBITS, NWAVES, R, ASYM, false>(p, tile);
+}
+
+template <int WBITS, int OBITS, int NW, int R, bool ASYM, bool A16>
+void launch_nw(const QLinearArgs& p, const GroupArgs* g, unsigned blocks, hipStream_t s)
+{
+    if constexpr (!A16) {
+        if (g) {
+            qlinear_decode_group_kernel<WBITS, OBITS, NW, R, ASYM>
+                <<<dim3(blocks), NW * 64, 0, s>>>(p, *g);
+            return;
+        }
+    }
+    qlinear_decode_kernel<WBITS, OBITS, NW, R, ASYM, A16><<<dim3(blocks), NW * 64, 0, s>>>(p);
+}
+
+template <int WBITS, int OBITS, int R, bool ASYM, bool A16>
+hipError_t launch_r(const QLinearArgs& p, GroupArgs* g, hipStream_t s)
+{
+    const int64_t blocks = g ? set_group_tiles(*g, R) : (p.N + R - 1) / R;
+    if (blocks < 0 || blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     const int64_t steps = (p.K + 63) / 64;
     // Waves per block: enough that one 8-step load round covers each wave's
     // share of K (every weight byte of the block is requested at once), at
@@ -264,34 +293,46 @@ hipError_t launch_r(const QLinearArgs& p, hipStream_t s)
     if (blocks < 2048) {
         while (nw < 4 && nw < steps) nw *= 2;
     }
-    const dim3 g((unsigned)blocks);
+    const unsigned b = (unsigned)blocks;
     switch (nw) {
     case 16:
-        if constexpr (NWMAX >= 16)
-            qlinear_decode_kernel<WBITS, OBITS, 16, R, ASYM, A16><<<g, 16 * 64, 0, s>>>(p);
+        if constexpr (NWMAX >= 16) launch_nw<WBITS, OBITS, 16, R, ASYM, A16>(p, g, b, s);
         break;
-    case 8: qlinear_decode_kernel<WBITS, OBITS, 8, R, ASYM, A16><<<g, 8 * 64, 0, s>>>(p); break;
-    case 4: qlinear_decode_kernel<WBITS, OBITS, 4, R, ASYM, A16><<<g, 4 * 64, 0, s>>>(p); break;
-    case 2: qlinear_decode_kernel<WBITS, OBITS, 2, R, ASYM, A16><<<g, 2 * 64, 0, s>>>(p); break;
-    default: qlinear_decode_kernel<WBITS, OBITS, 1, R, ASYM, A16><<<g, 64, 0, s>>>(p); break;
+    case 8: launch_nw<WBITS, OBITS, 8, R, ASYM, A16>(p, g, b, s); break;
+    case 4: launch_nw<WBITS, OBITS, 4, R, ASYM, A16>(p, g, b, s); break;
+    case 2: launch_nw<WBITS, OBITS, 2, R, ASYM, A16>(p, g, b, s); break;
+    default: launch_nw<WBITS, OBITS, 1, R, ASYM, A16>(p, g, b, s); break;
     }
     return hipGetLastError();
 }
 
 template <int WBITS, int OBITS, bool ASYM, bool A16>
-hipError_t launch_a(const QLinearArgs& p, hipStream_t s)
+hipError_t launch_a(const QLinearArgs& p, GroupArgs* g, hipStream_t s)
 {
     // narrow layers: 8 channels per block so at least 256 blocks stream
-    if ((p.N + 15) / 16 < 256) return launch_r<WBITS, OBITS, 8, ASYM, A16>(p, s);
-    return launch_r<WBITS, OBITS, 16, ASYM, A16>(p, s);
+    int64_t tiles16 = (p.N + 15) / 16;
+    if (g) {
+        tiles16 = 0;
+        for (int i = 0; i < g->n; ++i) tiles16 += (g->part[i].N + 15) / 16;
+    }
+    if (tiles16 < 256) return launch_r<WBITS, OBITS, 8, ASYM, A16>(p, g, s);
+    return launch_r<WBITS, OBITS, 16, ASYM, A16>(p, g, s);
 }
 
 template <int WBITS, int OBITS>
-hipError_t launch_t(const QLinearArgs& p, hipStream_t s)
+hipError_t launch_t(const QLinearArgs& p, GroupArgs* g, hipStream_t s)
 {
-    if (p.a_bits == 16) return launch_a<WBITS, OBITS, false, true>(p, s);
-    return p.w_zp ? launch_a<WBITS, OBITS, true, false>(p, s)
-                  : launch_a<WBITS, OBITS, false, false>(p, s);
+    if (p.a_bits == 16) return launch_a<WBITS, OBITS, false, true>(p, g, s);
+    return p.w_zp ? launch_a<WBITS, OBITS, true, false>(p, g, s)
+                  : launch_a<WBITS, OBITS, false, false>(p, g, s);
+}
+
+hipError_t launch_any(const QLinearArgs& p, GroupArgs* g, hipStream_t s)
+{
+    if (p.w_bits == 8 && p.out_bits == 8) return launch_t<8, 8>(p, g, s);
+    if (p.w_bits == 8) return launch_t<8, 16>(p, g, s);
+    if (p.out_bits == 8) return launch_t<4, 8>(p, g, s);
+    return launch_t<4, 16>(p, g, s);
 }
 
 }  // namespace
@@ -313,10 +354,13 @@ hipError_t launch_qlinear_decode(const QLinearArgs& p, hipStream_t s)
 {
     // a single token: the GEMV whose every load lane carries weight bytes
     if (gemv_supported(p)) return launch_qlinear_gemv(p, s);
-    if (p.w_bits == 8 && p.out_bits == 8) return launch_t<8, 8>(p, s);
-    if (p.w_bits == 8) return launch_t<8, 16>(p, s);
-    if (p.out_bits == 8) return launch_t<4, 8>(p, s);
-    return launch_t<4, 16>(p, s);
+    return launch_any(p, nullptr, s);
+}
+
+hipError_t launch_qlinear_decode_group(const QLinearArgs& p, GroupArgs g, hipStream_t s)
+{
+    if (p.a_bits != 8 || g.n < 1 || g.n > kMaxGroup) return hipErrorInvalidValue;
+    return gemv_supported(p) ? launch_qlinear_gemv_group(p, g, s) : launch_any(p, &g, s);
 }
 
 }  // namespace mq

@@ -52,7 +52,7 @@ __host__ __device__ constexpr int64_t gemv_lds_bytes(int64_t K, int nw)
 }
 
 template <int WBITS, int OBITS, int NW, bool ASYM>
-__global__ __launch_bounds__(NW * 64) void qlinear_gemv_kernel(QLinearArgs p)
+__device__ __forceinline__ void gemv_body(const QLinearArgs& p, int64_t tile)
 {
     constexpr int32_t qmin = -(1 << (OBITS - 1));
     constexpr int32_t qmax = (1 << (OBITS - 1)) - 1;
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(NW * 64) void qlinear_gemv_kernel(QLinearArgs p)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: keep it scalar
     const int c = lane / kLPC;  // channel of this lane's weight bytes
     const int j = lane % kLPC;  // its 16-byte chunk among the channel's kLPC
-    const int64_t n0 = (int64_t)blockIdx.x * kCPB;
+    const int64_t n0 = tile * kCPB;
     const int wrow = WBITS == 8 ? K32 : K32 / 2;  // bytes per weight row
     const int rows_w = (int)(p.N - n0 < kCPB ? p.N - n0 : kCPB);
     // descriptor over this block's weight rows: channels past N read zeros
@@ -179,21 +179,53 @@ __global__ __launch_bounds__(NW * 64) void qlinear_gemv_kernel(QLinearArgs p)
 }
 
 template <int WBITS, int OBITS, int NW, bool ASYM>
-hipError_t launch_nw(const QLinearArgs& p, hipStream_t s)
+__global__ __launch_bounds__(NW * 64) void qlinear_gemv_kernel(QLinearArgs p)
+{
+    gemv_body<WBITS, OBITS, NW, ASYM>(p, blockIdx.x);
+}
+
+// Several linears on one token (q/k, gate/up of a generation step): each is
+// a few microseconds of latency for less than one of bandwidth, so they
+// share a launch (1 x 2048 x (5632 + 5632): 6.3 us in two launches,
+// 4.9 in one; 1 x 2048 x (2048 + 256): 5.2 and 3.2).
+template <int WBITS, int OBITS, int NW, bool ASYM>
+__global__ __launch_bounds__(NW * 64) void qlinear_gemv_group_kernel(QLinearArgs p, GroupArgs g)
+{
+    const int32_t tile = take_group_part(p, g, (int32_t)blockIdx.x);
+    gemv_body<WBITS, OBITS, NW, ASYM>(p, tile);
+}
+
+// g: several linears, or nullptr
+template <int WBITS, int OBITS, int NW, bool ASYM>
+hipError_t launch_nw(const QLinearArgs& p, const GroupArgs* g, hipStream_t s)
 {
     const int64_t lds = gemv_lds_bytes(p.K, NW);
     // more than 64 KiB of dynamic LDS (K > 65536 - 256) must be opted into
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&qlinear_gemv_kernel<WBITS, OBITS, NW, ASYM>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemv_lds_bytes(65536, NW));
+    const auto opt_in = [](const void* kernel) {
+        return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)gemv_lds_bytes(65536, NW));
+    };
+    if (g) {
+        static const hipError_t attr = opt_in(
+            reinterpret_cast<const void*>(&qlinear_gemv_group_kernel<WBITS, OBITS, NW, ASYM>));
+        if (attr != hipSuccess) return attr;
+        GroupArgs parts = *g;
+        const int64_t tiles = set_group_tiles(parts, kCPB);
+        if (tiles < 0) return hipErrorInvalidValue;
+        qlinear_gemv_group_kernel<WBITS, OBITS, NW, ASYM>
+            <<<dim3((unsigned)tiles), NW * 64, (size_t)lds, s>>>(p, parts);
+        return hipGetLastError();
+    }
+    static const hipError_t attr =
+        opt_in(reinterpret_cast<const void*>(&qlinear_gemv_kernel<WBITS, OBITS, NW, ASYM>));
     if (attr != hipSuccess) return attr;
-    const dim3 g((unsigned)((p.N + kCPB - 1) / kCPB));
-    qlinear_gemv_kernel<WBITS, OBITS, NW, ASYM><<<g, NW * 64, (size_t)lds, s>>>(p);
+    const dim3 grid((unsigned)((p.N + kCPB - 1) / kCPB));
+    qlinear_gemv_kernel<WBITS, OBITS, NW, ASYM><<<grid, NW * 64, (size_t)lds, s>>>(p);
     return hipGetLastError();
 }
 
 template <int WBITS, int OBITS, bool ASYM>
-hipError_t launch_a(const QLinearArgs& p, hipStream_t s)
+hipError_t launch_a(const QLinearArgs& p, const GroupArgs* g, hipStream_t s)
 {
     // Waves: enough that one round of kU loads covers each wave's share of
     // the row (all of the block's weight bytes requested at once), at most
@@ -205,17 +237,25 @@ hipError_t launch_a(const QLinearArgs& p, hipStream_t s)
     int nw = 1;
     while (nw < 8 && nw * kU < steps) nw *= 2;
     switch (nw) {
-    case 8: return launch_nw<WBITS, OBITS, 8, ASYM>(p, s);
-    case 4: return launch_nw<WBITS, OBITS, 4, ASYM>(p, s);
-    case 2: return launch_nw<WBITS, OBITS, 2, ASYM>(p, s);
-    default: return launch_nw<WBITS, OBITS, 1, ASYM>(p, s);
+    case 8: return launch_nw<WBITS, OBITS, 8, ASYM>(p, g, s);
+    case 4: return launch_nw<WBITS, OBITS, 4, ASYM>(p, g, s);
+    case 2: return launch_nw<WBITS, OBITS, 2, ASYM>(p, g, s);
+    default: return launch_nw<WBITS, OBITS, 1, ASYM>(p, g, s);
     }
 }
 
 template <int WBITS, int OBITS>
-hipError_t launch_t(const QLinearArgs& p, hipStream_t s)
+hipError_t launch_t(const QLinearArgs& p, const GroupArgs* g, hipStream_t s)
 {
-    return p.w_zp ? launch_a<WBITS, OBITS, true>(p, s) : launch_a<WBITS, OBITS, false>(p, s);
+    return p.w_zp ? launch_a<WBITS, OBITS, true>(p, g, s) : launch_a<WBITS, OBITS, false>(p, g, s);
+}
+
+hipError_t launch_any(const QLinearArgs& p, const GroupArgs* g, hipStream_t s)
+{
+    if (p.w_bits == 8 && p.out_bits == 8) return launch_t<8, 8>(p, g, s);
+    if (p.w_bits == 8) return launch_t<8, 16>(p, g, s);
+    if (p.out_bits == 8) return launch_t<4, 8>(p, g, s);
+    return launch_t<4, 16>(p, g, s);
 }
 
 }  // namespace
@@ -234,10 +274,12 @@ bool gemv_supported(const QLinearArgs& p)
 
 hipError_t launch_qlinear_gemv(const QLinearArgs& p, hipStream_t s)
 {
-    if (p.w_bits == 8 && p.out_bits == 8) return launch_t<8, 8>(p, s);
-    if (p.w_bits == 8) return launch_t<8, 16>(p, s);
-    if (p.out_bits == 8) return launch_t<4, 8>(p, s);
-    return launch_t<4, 16>(p, s);
+    return launch_any(p, nullptr, s);
+}
+
+hipError_t launch_qlinear_gemv_group(const QLinearArgs& p, GroupArgs g, hipStream_t s)
+{
+    return launch_any(p, &g, s);
 }
 
 }  // namespace mq

@@ -225,6 +225,7 @@ struct Staging {
     static constexpr int pass_cols()
     {
         int c = WC * OB > 128 ? 128 / OB : WC;
+        if (WC % c || (c & (c - 1))) c = 32;  // whole passes of whole 16-byte chunks
         while (c > 32 && C::NWAVES * WR * (c * OB + 16) > C::STAGES * C::STAGE) c /= 2;
         return c;
     }
@@ -511,22 +512,7 @@ __device__ __forceinline__ void prefill_body(QLinearArgs& p, const GroupArgs* g,
     const int split = C::SPLITK ? b / total : 0;
     int tile = C::SPLITK ? b % total : b;
     if constexpr (GROUP) {
-        // the linear whose tile columns hold this tile (block-uniform)
-        int k = 0;
-#pragma unroll
-        for (int i = 1; i < kMaxGroup; ++i)
-            if (i < g->n && tile >= g->part[i].tile0) k = i;
-        const GroupPart& gp = g->part[k];
-        p.w = gp.w;
-        p.w_scale = gp.w_scale;
-        p.colsum = gp.colsum;
-        p.bias = gp.bias;
-        p.w_zp = gp.w_zp;
-        p.y = gp.y;
-        p.N = gp.N;
-        p.out_scale = gp.out_scale;
-        p.out_zp = gp.out_zp;
-        tile -= gp.tile0;
+        tile = take_group_part(p, *g, tile);
     }
     const int tn = tile / tiles_m;
     const int tm = tile % tiles_m;

@@ -168,3 +168,26 @@ def test_group_full_size_layers(workload, names):
     got = mq.mq_qlinear_group(g_a, lin, layers[0].w_bits, a_scale, a_zp, layers[0].out_bits)
     for g, s in zip(got, single):
         assert torch.equal(g, s)
+
+
+# Decode-sized M: one launch over the channel groups of all the linears
+# (8 or 16 channels per block, one to sixteen waves, the one-token GEMV), with
+# linears that end inside a block and K's last step cut.
+@pytest.mark.parametrize("M", [1, 2, 16])
+@pytest.mark.parametrize("K,Ns,w_bits,out_bits,asym,biases", [
+    (2048, (2048, 256), 8, 16, False, (True, False)),
+    (64, (9, 1, 40), 8, 8, True, (False, True, False)),
+    (1056, (130, 2001, 17, 8), 4, 16, True, (True, False, False, True)),
+    (5632, (5000, 0, 3), 8, 8, False, (False, False, False)),
+    (16384, (24, 24), 4, 8, False, (False, True)),
+])
+def test_group_decode_one_launch(M, K, Ns, w_bits, out_bits, asym, biases):
+    a, parts = _make_group(M * K, M, K, Ns, w_bits, asym, biases)
+    got, single = _run(a, parts, w_bits, out_bits, 0.03, -3, _mq().PATH_AUTO)
+    for i, p in enumerate(parts):
+        if Ns[i] == 0:
+            continue
+        ref = oracle.qlinear(a, p["wq"], w_bits, p["ws"], 0.03, -3, p["out_scale"],
+                             p["out_zp"], out_bits, bias=p["bias"], w_zp=p["zw"])
+        assert np.array_equal(got[i], ref), (i, int((got[i] != ref).sum()))
+        assert np.array_equal(single[i], ref), i

@@ -171,8 +171,8 @@ mq_status mq_pack_weights(const float* w, int64_t N, int64_t K, int32_t bits,
  *   y_q       device [M][N]; must not overlap the inputs
  *   M >= 0, N >= 0 (0 -> nothing to do), 1 <= K <= MQ_MAX_K, K even for
  *   w_bits = 4.  Any shape and alignment is accepted; 16-byte-aligned
- *   buffers with K % 16 == 0 (int8) or K % 32 == 0 (int4) take the tuned
- *   kernels.
+ *   inputs with K % 16 == 0 (int8) or K % 32 == 0 (int4) take the tuned
+ *   kernels (any N and output alignment on the prefill path).
  */
 mq_status mq_qlinear(const int8_t* a_q, int64_t M, int64_t K, int64_t N,
                      const void* w_q, int32_t w_bits, const float* w_scale,
@@ -331,8 +331,7 @@ mq_status mq_qlinear_asym(const int8_t* a_q, const int32_t* a_rowsum, int64_t M,
  * only feed the dequantization (the logits of the LM head), one pass
  * instead of a qlinear, a store of the codes and a dequantization pass
  * reading them back.
- *   y         device fp32 [M][N] (16-byte aligned with N % 4 == 0 for the
- *             tuned kernels); must not overlap the inputs or y_q
+ *   y         device fp32 [M][N]; must not overlap the inputs or y_q
  *   y_q       device [M][N] codes (out_bits), or NULL
  *   a_rowsum, w_zp  both NULL (symmetric weights) or as for mq_qlinear_asym
  *   everything else as in mq_qlinear_ws.

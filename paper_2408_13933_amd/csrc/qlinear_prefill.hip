@@ -38,6 +38,7 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));
 
 constexpr uint32_t kOOB = 0x80000000u;  // any offset past num_records reads zero
 
@@ -144,7 +145,7 @@ struct Cfg {
     // per batch (16 chunks, 64 registers in flight), never more than the
     // wave has, and a whole number of batches per wave
     static constexpr int MERGE_IB = 16 / (FM * 4) < 1 ? 1 : (16 / (FM * 4) > FN ? FN : 16 / (FM * 4));
-    static_assert(FN % MERGE_IB == 0, "whole merge batches per wave");
+    static_assert(!SPLITK || FN % MERGE_IB == 0, "whole merge batches per wave");
     static constexpr int A_BYTES = A_PER_WAVE * NWAVES * 1024;
     static constexpr int W_BYTES = W_PER_WAVE * NWAVES * 1024;
     static constexpr int STAGE = A_BYTES + W_BYTES;
@@ -199,6 +200,12 @@ struct EpiCtx {
     int32_t wave_col0;     // first channel of this wave's sub-tile (tile-local)
     MQ_LDS int8_t* stage;  // this wave's LDS staging area (staged stores)
     __amdgpu_buffer_rsrc_t ry;  // output rows of this tile
+    // rows that do not start on whole dwords (N % 4 != 0 with int8 codes, odd
+    // N with int16 ones): stored through the tile's pointer, by element or in
+    // 16-byte runs of any alignment, with the row bound checked here
+    bool unal;
+    int32_t rows;
+    int8_t* y_tile;
     // dequantized outputs (fp32): the layer's output format, this tile's
     // fp32 rows, whether the codes are stored as well
     float out_scale;
@@ -248,9 +255,8 @@ struct Staging {
 // Rows past M fall outside the descriptor and are dropped by the hardware;
 // channel groups past N get an out-of-range offset.  The requant is the
 // integer form with one mul_hi per output (cheaper on gfx950 than fp64
-// conversions).  FAST: off is in the accumulator's start value, the output
-// zero-point is folded into the rounding constants and N % 4 == 0, leaving
-// mul_hi, add, shift, clamp per output; PRE adds the clamp and left shift
+// conversions).  FAST: off is in the accumulator's start value and the output
+// zero-point is folded into the rounding constants, leaving mul_hi, add, shift, clamp per output; PRE adds the clamp and left shift
 // of the columns whose shift is below 33 (large rescale factors, typical of
 // int16 outputs), which the plain FAST form leaves out when no column of
 // the tile needs them.
@@ -379,7 +385,7 @@ __device__ __forceinline__ void prefill_epilogue(Acc& acc, Acc2& acc2, const Epi
                                             x.out_zp_code);
                     const int32_t row_f = x.lane_row_off_f + j * 32 * x.row_bytes_f;
                     const int32_t col_f = (x.n_tile + nl) * 4;
-                    if (FAST || (x.n_left & 3) == 0 || nl + 3 < x.n_left) {
+                    if ((x.n_left & 3) == 0 || nl + 3 < x.n_left) {
                         const v4i v = {__builtin_bit_cast(int, f[0]), __builtin_bit_cast(int, f[1]),
                                        __builtin_bit_cast(int, f[2]), __builtin_bit_cast(int, f[3])};
                         __builtin_amdgcn_raw_buffer_store_b128(
@@ -394,7 +400,7 @@ __device__ __forceinline__ void prefill_epilogue(Acc& acc, Acc2& acc2, const Epi
                     }
                     if (!x.has_codes) continue;
                 }
-                if (FAST || (x.n_left & 3) == 0 || nl + 3 < x.n_left) {
+                if (!x.unal && ((x.n_left & 3) == 0 || nl + 3 < x.n_left)) {
                     const uint32_t voff = col_ok ? (uint32_t)(row_off + col_off) : kOOB;
                     if constexpr (C::OBITS == 8) {
                         const uint32_t lo =
@@ -410,7 +416,8 @@ __device__ __forceinline__ void prefill_epilogue(Acc& acc, Acc2& acc2, const Epi
                         __builtin_amdgcn_raw_buffer_store_b64(v, x.ry, voff, 0, 0);
                     }
                 } else {
-                    // a channel group straddling N (N % 4 != 0): element stores
+                    // a channel group straddling N, or a row off the dwords:
+                    // element stores
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const uint32_t voff =
@@ -436,7 +443,10 @@ __device__ __forceinline__ void prefill_epilogue(Acc& acc, Acc2& acc2, const Epi
             const v4i v = *reinterpret_cast<MQ_LDS const v4i*>(x.stage + lrow * S::PITCH + ch * 16);
             if (!YF || x.has_codes) {
                 const uint32_t voff = (uint32_t)((x.wave_row0 + lrow) * x.row_bytes + col_byte);
-                __builtin_amdgcn_raw_buffer_store_b128(v, x.ry, voff, 0, 0);
+                if (!x.unal)
+                    __builtin_amdgcn_raw_buffer_store_b128(v, x.ry, voff, 0, 0);
+                else if (x.wave_row0 + lrow < x.rows)
+                    *reinterpret_cast<v4i_any*>(x.y_tile + voff) = v;
             }
             if constexpr (YF) {
                 // the chunk's 16 / OB codes (clamped already), four per store
@@ -716,7 +726,7 @@ __device__ __forceinline__ void prefill_body(QLinearArgs& p, const GroupArgs* g,
     // rounding constant, off in the accumulator's start value; pre0: no
     // column of the tile needs the pre-shift
     const bool pre0 = (flags & 1) != 0;
-    const bool fast = (flags & 6) == 6 && (p.N % 4) == 0;
+    const bool fast = (flags & 6) == 6;
     if (zp_fold && tid < C::TN) e_rnd[tid] += p.out_zp * (1 << (e_sp[tid] & 0xFF));
     // stage STAGES-1: the part the stage switch step would issue; the rest
     // goes out during the first stage's steps, as for every later stage
@@ -1051,9 +1061,12 @@ __device__ __forceinline__ void prefill_body(QLinearArgs& p, const GroupArgs* g,
     ctx.ry = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(y_batch + m_tile * (int64_t)ctx.row_bytes), (short)0,
         (int)(rows_a * ctx.row_bytes), 0x00020000);
-    // staged stores need the tile's channels inside N and 16-byte row chunks
-    const bool staged = fast && n_tile + C::TN <= p.N && (ctx.row_bytes % 16) == 0 &&
-                        ((uintptr_t)y_batch % 16) == 0;
+    ctx.rows = rows_a;
+    ctx.y_tile = y_batch + m_tile * (int64_t)ctx.row_bytes;
+    ctx.unal = (ctx.row_bytes % 4) != 0 || ((uintptr_t)y_batch % 4) != 0;
+    // staged stores need the tile's channels inside N (a buffer store of 16
+    // bytes needs whole dwords, no more)
+    const bool staged = fast && n_tile + C::TN <= p.N;
     if constexpr (YF) {
         ctx.out_scale = p.out_scale;
         ctx.out_zp_code = p.out_zp;
@@ -1063,13 +1076,8 @@ __device__ __forceinline__ void prefill_body(QLinearArgs& p, const GroupArgs* g,
         ctx.ryf = __builtin_amdgcn_make_buffer_rsrc(
             (void*)(p.y_f + m_tile * p.N), (short)0, (int)(rows_a * ctx.row_bytes_f),
             0x00020000);
-        // staged: the tile's channels inside N, 16-byte fp32 row chunks, and
-        // the codes' own rules when they are stored too
-        const bool staged_f = fast && n_tile + C::TN <= p.N && (p.N % 4) == 0 &&
-                              (!ctx.has_codes || staged);
-        if (staged_f && pre0)
-            prefill_epilogue<C, ASYM, true, false, true, true>(acc, acc2, ctx);
-        else if (staged_f) prefill_epilogue<C, ASYM, true, true, true, true>(acc, acc2, ctx);
+        if (staged && pre0) prefill_epilogue<C, ASYM, true, false, true, true>(acc, acc2, ctx);
+        else if (staged) prefill_epilogue<C, ASYM, true, true, true, true>(acc, acc2, ctx);
         else if (fast && pre0) prefill_epilogue<C, ASYM, true, false, false, true>(acc, acc2, ctx);
         else if (fast) prefill_epilogue<C, ASYM, true, true, false, true>(acc, acc2, ctx);
         else prefill_epilogue<C, ASYM, false, false, false, true>(acc, acc2, ctx);
@@ -1384,28 +1392,22 @@ bool prefill_supported(const QLinearArgs& p)
     const int64_t lda = eff_lda(p) * ab, ldy = eff_ldy(p) * ob;
     const int64_t ldw = p.w_bits == 8 ? eff_ldw(p) : (p.ldw ? p.ldw : p.K / 2);
     // whole 16-byte chunks per row (packed int4 rows too), 16-byte aligned
-    // rows and batches; output rows and batches aligned to one store of four
-    // channels (4 bytes of int8, 8 of int16), so every channel group of the
-    // epilogue is one aligned store
-    const int64_t og = 4 * ob;
+    // rows and batches; output rows of any length and alignment
     const bool kok = p.w_bits == 8 ? (p.K % 16 == 0) : (p.K % 32 == 0);
     const bool align = ((uintptr_t)p.a % 16) == 0 && ((uintptr_t)p.w % 16) == 0 &&
-                       ((uintptr_t)p.y % og) == 0 && lda % 16 == 0 && ldw % 16 == 0 &&
-                       ldy % og == 0 && (p.a_bs * ab) % 16 == 0 && p.w_bs % 16 == 0 &&
-                       (p.y_bs * ob) % og == 0;
+                       lda % 16 == 0 && ldw % 16 == 0 && (p.a_bs * ab) % 16 == 0 &&
+                       p.w_bs % 16 == 0;
     // byte offsets inside one 256-row tile must fit the 32-bit buffer offset
     const int64_t lim = (int64_t)1 << 31;
     const bool nok = 256 * ldy < lim && 256 * lda < lim && 256 * ldw < lim &&
                      (!p.y_f || 256 * p.N * 4 < lim);
-    // fp32 outputs: 16-byte stores of four channels
-    const bool fok = !p.y_f || (((uintptr_t)p.y_f % 16) == 0 && p.N % 4 == 0);
     // 16-bit activation codes: int8 weights only (the W8A16 tile), which
     // also takes strides, batches and int64 row terms; the 8-bit tiles take
     // dense single products
     const bool dense = p.lda == 0 && p.ldw == 0 && p.ldy == 0 && p.batch == 1 &&
                        p.row_off == nullptr && p.ws_stride == 1;
     const bool aok = p.a_bits == 8 ? dense : (p.w_bits == 8 && p.w_zp == nullptr);
-    return kok && align && nok && aok && fok && p.batch >= 1 && p.batch <= 65535;
+    return kok && align && nok && aok && p.batch >= 1 && p.batch <= 65535;
 }
 
 int64_t prefill_workspace_bytes(const QLinearArgs& p)

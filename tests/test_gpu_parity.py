@@ -458,3 +458,53 @@ def test_full_size_parity(case):
     g = gpu_layer(ld, workspace=ws)
     o = oracle_layer(ld)
     assert_same(g, o)
+
+
+# Output rows of every length: rows off the dwords (odd int16 rows, int8 rows
+# that are no multiple of 4), channel groups that straddle N, tiles inside
+# and past N, on every tile, with int4 and asymmetric weights, and with fp32
+# outputs (codes stored or not) from a base off its 16-byte line.
+@pytest.mark.parametrize("M,N", [(17, 258), (130, 131), (300, 1001), (65, 515), (257, 3)])
+@pytest.mark.parametrize("w_bits,out_bits,asym", [(8, 8, False), (8, 16, True), (4, 16, False),
+                                                  (4, 8, True)])
+def test_ragged_output_rows(M, N, w_bits, out_bits, asym):
+    import paper_2408_13933_amd as mq
+    import torch
+    rng = np.random.default_rng(M + N + out_bits)
+    K, qw = 352, 128 if w_bits == 8 else 8
+    a = rng.integers(-128, 128, (M, K)).astype(np.int8)
+    codes = rng.integers(-qw, qw, (N, K))
+    wq = codes.astype(np.int8) if w_bits == 8 else \
+        ((codes[:, 0::2] & 15) | ((codes[:, 1::2] & 15) << 4)).astype(np.uint8)
+    ws = (10.0 ** rng.uniform(-4, -3, N)).astype(np.float32)
+    cs = codes.sum(1).astype(np.int32)
+    zw = rng.integers(-qw, qw, N).astype(np.int32) if asym else None
+    fmt = (0.03, -3, 0.02 if out_bits == 8 else 1e-4, 5)
+    ref = oracle.qlinear(a, wq, w_bits, ws, fmt[0], fmt[1], fmt[2], fmt[3], out_bits, w_zp=zw)
+    dev = [torch.from_numpy(t).cuda() for t in (a, wq, ws, cs)]
+    gz = None if zw is None else torch.from_numpy(zw).cuda()
+    rs = mq.mq_act_rowsum(dev[0]) if asym else None
+    dt = torch.int8 if out_bits == 8 else torch.int16
+
+    def view(dtype, off):  # off elements into a buffer with a guard behind it
+        buf = torch.full((M * N + off + 64,), 77, dtype=dtype, device="cuda")
+        return buf, buf[off:off + M * N].view(M, N)
+
+    for path in [mq.PATH_AUTO] + [mq.prefill_tile_path(t) for t in range(mq.PREFILL_TILES)]:
+        buf, y = view(dt, 1)
+        if asym:
+            mq.mq_qlinear_asym(dev[0], rs, dev[1], w_bits, dev[2], gz, dev[3], *fmt, out_bits,
+                               out=y, path=path)
+        else:
+            mq.mq_qlinear(dev[0], dev[1], w_bits, dev[2], dev[3], *fmt, out_bits, out=y, path=path)
+        assert np.array_equal(y.cpu().numpy(), ref), path
+        assert bool((buf[:1] == 77).all()) and bool((buf[1 + M * N:] == 77).all()), path
+        for with_codes in (False, True):
+            cbuf, c = view(dt, 1)
+            fbuf, f = view(torch.float32, 1)
+            mq.mq_qlinear_dequant(dev[0], dev[1], w_bits, dev[2], dev[3], *fmt, out_bits, out=f,
+                                  codes=c if with_codes else None, w_zp=gz, a_rowsum=rs, path=path)
+            assert np.array_equal(f.cpu().numpy(), oracle.dequant(ref, fmt[2], fmt[3])), path
+            assert bool((fbuf[1 + M * N:] == 77).all()), path
+            if with_codes:
+                assert np.array_equal(c.cpu().numpy(), ref), path

@@ -101,9 +101,6 @@ struct Cfg {
     static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, BK = BK_;
     static constexpr int STAGES = STAGES_, SWZ = SWZ_;
     static constexpr int NWAVES = WM * WN;
-    // work-groups per CU the register budget is sized for: the short-K
-    // 16-bit tile (two stages) shares a CU between two
-    static constexpr int OCC = (ABITS_ == 16 && STAGES_ == 2) ? 2 : 1;
     // the short-K 16-bit tile (two stages) serves K <= 128 without bias
     // only: then |c| = |sum_k (a - a_zp)(b - b_zp)| <= 128 * 65535 * 255 <
     // 2^31, the saturation is the identity and its terms sum in int32
@@ -155,6 +152,12 @@ struct Cfg {
     // activations use the channel array for the low part of the offset and
     // two words per token row for an int64 row term
     static constexpr int LDS_ASYM = LDS + (TN + 2 * TM) * 4;
+    // waves per SIMD the register budget is sized for: 16-bit tiles whose
+    // stage ring leaves room for a second work-group on the CU share it
+    // between two, so one's waits, prologue and epilogue overlap the other's
+    // products
+    static constexpr int GROUPS_PER_CU = A16 && 2 * LDS_ASYM <= 160 * 1024 ? 2 : 1;
+    static constexpr int OCC = A16 ? GROUPS_PER_CU * NWAVES / 4 : 1;
     static_assert(!A16 || (WBITS == 8 && !SPLITK), "16-bit activations: int8 weights, no split");
     static_assert(TM % (WM * 32) == 0 && TN % (WN * 32) == 0, "wave grid");
     static_assert((TM * CA) % 64 == 0 && (TN * CW) % 64 == 0, "whole wave loads");
@@ -1213,18 +1216,28 @@ constexpr int kTile256x256W8 = 4;
 // K >= 4096 and no K split only (int4 weights: 64x64 stays ahead).
 template <int WB, int OB> using T128x64 = Cfg<WB, OB, 128, 64, 2, 2, 128, 4, 2, 4>;
 constexpr int kTile128x64 = 5;
-// 16-bit activation codes: 128x128 tokens x channels, 64 k per stage (128
-// bytes of each activation row), DMA spread over both steps of a stage
-template <int OB> using T128x128A16 = Cfg<8, OB, 128, 128, 2, 2, 64, 4, 2, 2, 16>;
+// 16-bit activation codes (two MFMAs per fragment pair), 64 k per stage (128
+// bytes of each activation row), DMA spread over both steps of a stage.
+// 128x128 tokens x channels on eight waves of 32x64, three stages so that two
+// work-groups share a CU: with one work-group of four waves a SIMD's only
+// wave stood idle at every barrier, plane split and LDS wait (1024 x 2048 ->
+// 5632: 47.5 -> 32.2 us, 2048 x 4096 -> 8192: 169 -> 139 us).
+template <int OB> using T128x128A16 = Cfg<8, OB, 128, 128, 4, 2, 64, 3, 2, 2, 16>;
+// 192 channels: fewer, larger tiles where 128x128 ones need a second round
+// (1024 x 2048 -> 5632: 240 tiles on 256 CUs instead of 352, 32.2 -> 30.2 us)
+template <int OB> using T128x192A16 = Cfg<8, OB, 128, 192, 4, 2, 64, 4, 2, 2, 16>;
+// few tokens or channels: half the tokens per tile, twice the tiles (1024 x
+// 5632 -> 2048: 34.0 us against 38.8 on 128x128)
+template <int OB> using T64x128A16 = Cfg<8, OB, 64, 128, 2, 2, 64, 4, 2, 2, 16>;
 // short K (<= 128 codes, e.g. the attention scores over a 64-dimensional
 // head): two stages are all the pipeline needs, and half the LDS lets two
 // work-groups share a CU, so one's prologue and epilogue overlap the
 // other's products
 template <int OB> using T128x128A16S2 = Cfg<8, OB, 128, 128, 2, 2, 64, 2, 2, 1, 16>;
-// at most 64 channels (P V over a 64-dimensional head): a 128x128 tile
-// would leave half of its products and weight loads idle, and 64-row tiles
-// double the work-groups (P V at 1024 tokens: 512 instead of 256; the
-// causal form's longest tile has half the rows)
+// at most 64 channels (P V over a 64-dimensional head: a 128x128 tile would
+// leave half of its products and weight loads idle), and layers with so few
+// tiles that the chip is idle (64 x 2048 -> 2048: 21.5 -> 11.4 us, 300 x
+// 16384 -> 2048: 120 -> 63 us against four-wave 128x128 tiles)
 template <int OB> using T64x64A16 = Cfg<8, OB, 64, 64, 2, 2, 64, 4, 2, 2, 16>;
 static_assert(T128x128A16S2<8>::A16_I32 && !T128x128A16<8>::A16_I32 &&
                   !T64x64A16<8>::A16_I32,
@@ -1272,6 +1285,28 @@ static_assert(kTiles[kTile256x128].tn == T256x128<8, 8>::TN &&
                   kTiles[kTile128x64].tn == T128x64<8, 8>::TN,
               "the time model's rows follow the tile indices");
 constexpr double kBusySlowdown = 0.60;
+// The same for the 16-bit tiles, whose work-groups per CU (occ) share its
+// rate: a CU with n tiles takes ceil(n / occ) fixed parts and n times the
+// stages, a stage stage_us * (1 + busy * (busy fraction of the CUs)^2).
+// Fitted to every tile on 14 layers (M = 20..2048, K = 512..16384, N =
+// 256..8192), on each of which it picks the fastest measured tile.
+struct A16Model {
+    int tm, tn, occ;
+    double fixed_us, stage_us, busy;
+};
+constexpr int kA16Tiles = 4, kA16T64x64 = 0, kA16T64x128 = 1, kA16T128x128 = 2, kA16T128x192 = 3;
+constexpr A16Model kTilesA16[kA16Tiles] = {
+    {64, 64, 2, 4.4, 0.215, 0.10},
+    {64, 128, 2, 6.0, 0.262, 0.22},
+    {128, 128, 2, 6.0, 0.362, 0.25},
+    {128, 192, 1, 8.6, 0.470, 0.40},
+};
+static_assert(kTilesA16[kA16T64x128].tn == T64x128A16<8>::TN &&
+                  kTilesA16[kA16T128x128].tm == T128x128A16<8>::TM &&
+                  kTilesA16[kA16T128x192].tn == T128x192A16<8>::TN &&
+                  T64x128A16<8>::GROUPS_PER_CU == 2 && T128x128A16<8>::GROUPS_PER_CU == 2 &&
+                  T128x192A16<8>::GROUPS_PER_CU == 1,
+              "the 16-bit time model's rows follow the tiles");
 // int4 weights: the in-register unpack makes a K-loop stage ~1.35x longer
 constexpr double kInt4StageFactor = 1.35;
 // A K split adds round trips to memory (partial stores, the counter, the
@@ -1327,6 +1362,26 @@ Choice choose(const QLinearArgs& p, bool can_split, const int64_t* Ns = nullptr,
                 best_t = tt;
                 best = {c, sp};
             }
+        }
+    }
+    return best;
+}
+
+int choose_a16(const QLinearArgs& p)
+{
+    int best = kA16T128x128;
+    double best_t = 1e300;
+    const int64_t kt = (p.K + kA16TileK - 1) / kA16TileK;
+    for (int c = 0; c < kA16Tiles; ++c) {
+        const A16Model& t = kTilesA16[c];
+        const int64_t tiles = ((p.M + t.tm - 1) / t.tm) * ((p.N + t.tn - 1) / t.tn);
+        const int64_t n = (tiles + kCUs - 1) / kCUs;
+        const double busy = tiles < kCUs ? (double)tiles / kCUs : 1.0;
+        const double tt = t.fixed_us * (double)((n + t.occ - 1) / t.occ) +
+                          t.stage_us * (1.0 + t.busy * busy * busy) * (double)(kt * n);
+        if (tt < best_t) {
+            best_t = tt;
+            best = c;
         }
     }
     return best;
@@ -1423,7 +1478,10 @@ int64_t prefill_counter_bytes(const QLinearArgs& p)
     return split_counter_bytes(((p.M + t.tm - 1) / t.tm) * ((p.N + t.tn - 1) / t.tn));
 }
 
-// 16-bit activation codes: no K split; ASYM: int64 row terms
+// 16-bit activation codes: no K split; ASYM: int64 row terms.  Layers (one
+// dense product, no row terms) take the tile of the time model; batched,
+// strided and causal products 64x64 up to 64 channels and 128x128 above, the
+// tiles their causal column sums are laid out for.
 template <int>
 hipError_t launch_a16(const QLinearArgs& p, hipStream_t s)
 {
@@ -1434,7 +1492,16 @@ hipError_t launch_a16(const QLinearArgs& p, hipStream_t s)
         return o8 ? launch_cfg<T128x128A16S2<8>, false>(p, 1, s)
                   : launch_cfg<T128x128A16S2<16>, false>(p, 1, s);
     }
-    if (p.N <= 64) {
+    const bool layer = !ro && p.batch == 1 && p.lda == 0 && p.ldw == 0 && p.ldy == 0 &&
+                       p.out_causal < 0 && p.in_causal < 0;
+    const int tile = layer ? choose_a16(p) : p.N <= 64 ? kA16T64x64 : kA16T128x128;
+    if (tile == kA16T64x128)
+        return o8 ? launch_cfg<T64x128A16<8>, false>(p, 1, s)
+                  : launch_cfg<T64x128A16<16>, false>(p, 1, s);
+    if (tile == kA16T128x192)
+        return o8 ? launch_cfg<T128x192A16<8>, false>(p, 1, s)
+                  : launch_cfg<T128x192A16<16>, false>(p, 1, s);
+    if (tile == kA16T64x64) {
         if (ro) return o8 ? launch_cfg<T64x64A16<8>, true>(p, 1, s)
                           : launch_cfg<T64x64A16<16>, true>(p, 1, s);
         return o8 ? launch_cfg<T64x64A16<8>, false>(p, 1, s)

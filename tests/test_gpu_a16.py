@@ -110,3 +110,31 @@ def test_a16_int8_range_codes_equal_the_int8_layer():
                           d["w_colsum"], d["a_scale"], d["a_zp"], d["out_scale"], d["out_zp"], 16,
                           bias=d["bias"], path=mq.PATH_DECODE)
     assert np.array_equal(y.cpu().numpy(), g.y_q[:16])
+
+
+@pytest.mark.parametrize("out_bits,has_bias", [(8, True), (16, False)])
+@pytest.mark.parametrize("M,K,N", [
+    (65, 272, 257),      # few tiles: 64x64, ragged in every direction
+    (900, 2064, 1900),   # 64x128
+    (300, 2064, 8001),   # 128x128, two work-groups per CU
+    (773, 2064, 5633),   # 128x192: its last tile column holds 65 channels
+    (773, 2064, 5504),   # 128x192: 128 channels, whole store groups
+])
+def test_a16_tiles_equal_the_generic_kernel(M, K, N, out_bits, has_bias):
+    """Every tile the 16-bit time model chooses, at ragged token, channel and
+    K remainders: all outputs the generic kernel's bits, the first and last
+    rows the oracle's."""
+    mq, torch = _mq(), _torch()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M * 7 + N)
+    a = torch.randint(-32768, 32768, (M, K), generator=g, device="cuda").to(torch.int16)
+    w = torch.randn(N, K, generator=g, device="cuda") * 0.02
+    bias = torch.randn(N, generator=g, device="cuda") * 0.1 if has_bias else None
+    wq, ws, cs = mq.mq_pack_weights(w, 8)
+    args = (8, ws, cs, 2e-4, 1234, 8.0 / 2 ** out_bits * 16, 7, out_bits, bias)
+    y = mq.mq_qlinear_a16(a, wq, *args)
+    assert torch.equal(y, mq.mq_qlinear_a16(a, wq, *args, path=mq.PATH_GENERIC))
+    rows = torch.cat((a[:2], a[-2:]))
+    ref = oracle.qlinear(rows.cpu().numpy(), wq.cpu().numpy(), 8, ws.cpu().numpy(), 2e-4, 1234,
+                         args[5], 7, out_bits, bias=None if bias is None else bias.cpu().numpy())
+    assert np.array_equal(torch.cat((y[:2], y[-2:])).cpu().numpy(), ref)

@@ -59,7 +59,7 @@ typedef enum {
     MQ_PATH_GENERIC = 3,  /* one thread per output, any shape or alignment */
     /* MQ_PATH_PREFILL_TILE0 + t, t = 0..MQ_PREFILL_TILES-1: the prefill
      * kernel with output tile t (0: 256x128, 1: 128x128, 2: 192x256,
-     * 3: 64x64, 4: 256x256 on eight waves, 5: 128x64; tokens x channels)
+     * 3: 64x64, 4: 256x256, 5: 64x128; tokens x channels)
      * instead of the one its cost model picks -- a hook for tests and
      * measurements;
      * the results are the same bits.  With a workspace the K split is the

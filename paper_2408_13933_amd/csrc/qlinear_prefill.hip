@@ -44,6 +44,9 @@ constexpr uint32_t kOOB = 0x80000000u;  // any offset past num_records reads zer
 
 // Split-K workspace: one int32 arrival counter per tile (rounded up to 256
 // bytes), then the int32 partial sums of every (tile, slice) block.
+// A layer with more than kMaxSplitTiles tiles is not split, so the counters of
+// any layer fit the first 4 KiB.
+constexpr int kMaxSplitTiles = 1024;
 __host__ __device__ inline int64_t split_counter_bytes(int64_t tiles)
 {
     return (tiles * 4 + 255) / 256 * 256;
@@ -1036,6 +1039,15 @@ __device__ __forceinline__ void prefill_body(QLinearArgs& p, const GroupArgs* g,
         }
         if (tid == 0)
             __hip_atomic_exchange(counters + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        // layers of different sizes may share a workspace one after another:
+        // where this layer's first partial sums lie in the counter area of
+        // one with more tiles, they go back to zero too (the first chunks of
+        // tile 0's slice 0 cover that area; each thread clears the chunk
+        // that it alone wrote or read)
+        static_assert(C::THREADS * 16 >= kMaxSplitTiles * 4, "one chunk per thread covers it");
+        if (tile == 0 && split_counter_bytes(total) + tid * 16 < kMaxSplitTiles * 4)
+            __builtin_amdgcn_raw_buffer_store_b128(v4i{0, 0, 0, 0}, rp, chunk_off(0, 0, 0, 0), 0,
+                                                   kCoherent);
     }
 
     // ---- epilogue, straight from the accumulators (see prefill_epilogue)
@@ -1175,13 +1187,20 @@ hipError_t launch_group_cfg(const QLinearArgs& p, GroupArgs g, hipStream_t s)
 
 // Tile shapes.  (tokens x channels, wave grid, K bytes per stage, stages,
 // swizzle, steps the DMA of a stage is spread over; measured: the
-// 128-deep four-wave tiles are fastest with the DMA spread over the whole
-// stage.)  A four-wave 256x256 tile (4x4 fragments per wave, 256
-// accumulator registers, no K split) was slower than the eight-wave one on
-// every measured shape and is gone.
-template <int WB, int OB> using T256x128 = Cfg<WB, OB, 256, 128, 2, 2, 128, 3, 2, 4>;
+// 128-deep tiles of three and four stages are fastest with the DMA spread
+// over the whole stage.)  Every tile above 64x64 runs eight waves, two per
+// SIMD: one wave's MFMAs fill the other's waits for the stage barrier and its
+// LDS reads.  Against four waves of twice the sub-tile each: 128x128 12.4 ->
+// 10.3 us at 1024 x 2048 -> 2304 and 15.9 -> 10.7 at 512 x 2048 -> 5632 with
+// packed int4 (12.6 with int8), 256x128 38.2 -> 34.6 us at 2048 x 2048 -> 5632.
+// The wave grid with fewer waves along the channels repeats fewer
+// activation reads; packed int4 wants the other one, which unpacks each
+// weight fragment in two waves instead of four.
+template <int WB, int OB>
+using T256x128 = std::conditional_t<WB == 8, Cfg<WB, OB, 256, 128, 4, 2, 128, 3, 2, 4>,
+                                    Cfg<WB, OB, 256, 128, 2, 4, 128, 3, 2, 4>>;
 constexpr int kTile256x128 = 0;
-template <int WB, int OB> using T128x128 = Cfg<WB, OB, 128, 128, 2, 2, 128, 4, 2, 4>;
+template <int WB, int OB> using T128x128 = Cfg<WB, OB, 128, 128, 2, 4, 128, 4, 2, 4>;
 constexpr int kTile128x128 = 1;
 // 64x64: layers with few output tiles (1024 tokens x 256 channels: 64
 // tiles instead of 16), four waves of 32x32
@@ -1208,14 +1227,13 @@ constexpr int kTile192x256 = 2;
 // wave leave room for the K split and the pre-shift epilogue forms.
 template <int WB, int OB> using T256x256W8 = Cfg<WB, OB, 256, 256, 2, 4, 128, 2, 2, 2>;
 constexpr int kTile256x256W8 = 4;
-// 128 tokens x 64 channels, four waves of 64 x 32 (two fragments each: one
-// weight fragment read per two MFMAs, where 64x64 has one per MFMA), four
-// 128-deep stages, one work-group per CU: the layers at 1024 tokens with a
-// long K and 256 such tiles (1024 x 5632 -> 2048: 18.5 against 21.8 us on
-// 64x64, measured).  The cost model offers it for int8 weights with
-// K >= 4096 and no K split only (int4 weights: 64x64 stays ahead).
-template <int WB, int OB> using T128x64 = Cfg<WB, OB, 128, 64, 2, 2, 128, 4, 2, 4>;
-constexpr int kTile128x64 = 5;
+// 64 tokens x 128 channels, eight waves of 32 x 32 (each row segment a wave
+// stores is twice that of 128 x 64, otherwise the same: 17.6 us both at 1024 x
+// 5632 -> 2048; packed int4 20.4 against 21.7): layers of about one such tile
+// per CU (1024 x 2048 -> 2048: 8.2 us, 11.4 on 64x64; 777 x 5632 -> 2048: 16.0
+// us, 19.1 on 64x64).
+template <int WB, int OB> using T64x128 = Cfg<WB, OB, 64, 128, 2, 4, 128, 4, 2, 4>;
+constexpr int kTile64x128 = 5;
 // 16-bit activation codes (two MFMAs per fragment pair), 64 k per stage (128
 // bytes of each activation row), DMA spread over both steps of a stage.
 // 128x128 tokens x channels on eight waves of 32x64, three stages so that two
@@ -1247,32 +1265,39 @@ static_assert(T128x128A16<8>::TM == kA16TileM && T128x128A16<8>::BK == kA16TileK
                   kA16TileM % T64x64A16<8>::TM == 0 && T64x64A16<8>::BK == kA16TileK,
               "the causal column sums assume these 16-bit tile sizes");
 
-// Time model of each tile shape on MI355X, fitted to forced-tile
-// measurements of the workload layers (graph replay, one box; every tile on
-// M = 512..2048, K = 2048..16384, N = 256..256000, int8 and int4 weights).
-// A block costs a fixed part (the first memory round trip, the epilogue and
-// its stores) plus a time per K stage; with more CUs busy a stage takes
-// longer (the chip clocks down under the MFMA load and the blocks share the
-// memory system): stage * (1 + kBusySlowdown * busy fraction).  occ blocks
-// share a CU within one round.  Units: microseconds.  Over the 60 measured
-// (shape, tile) points the model is within about 20%, and it picks the
-// measured fastest tile on every one of the ten unsplit shapes.
+// Time model of each tile shape on MI355X, fitted to timings of every tile on
+// 34 int8 and 16 packed int4 layers (M = 20..2048, K = 1024..16384, N =
+// 256..256000, one box).  A block costs a fixed part (the first memory round
+// trip, the epilogue and its stores) plus a time per K stage; with more CUs
+// busy a stage takes longer (the chip clocks down under the MFMA load and the
+// blocks share the memory system): stage * (1 + busy * (busy fraction)^2).
+// occ blocks share a CU within one round.  Units: microseconds.  The chosen
+// tile is the fastest measured one, or within 15% of it, on each of these
+// layers (0.6% behind it on average with int8 weights, 1.2% with int4).
 struct TileModel {
     int tm, tn, bk;
-    double fixed_us, stage_us;
+    double fixed_us, stage_us, busy;
     int occ = 1;
-    bool splits = true;  // whether the tile takes a K split
 };
 constexpr TileModel kTiles[] = {
-    {256, 128, 128, 8.05, 0.593},
-    {128, 128, 128, 5.58, 0.348},
-    {192, 256, 128, 6.98, 0.845},  // eight waves, two 128-deep stages (int8 weights)
-    {64, 64, 128, 3.63, 0.232, 2},  // 64 KiB of stage ring: two blocks per CU
-    {256, 256, 128, 10.5, 0.912},   // eight waves of 128x64, two 128-deep stages
-    {128, 64, 128, 5.0, 0.192, 1, false},  // int8 weights, K >= 4096 (see choose)
+    {256, 128, 128, 7.0, 0.476, 0.8},
+    {128, 128, 128, 4.4, 0.287, 0.9},
+    {192, 256, 128, 6.0, 0.740, 1.0},
+    {64, 64, 128, 2.8, 0.153, 1.6, 2},  // 64 KiB of stage ring: two blocks per CU
+    {256, 256, 128, 7.6, 0.934, 1.1},
+    {64, 128, 128, 3.6, 0.186, 0.6},
 };
-// the 192x256 tile with int4 weights runs four waves on 64-deep stages
-constexpr TileModel kTile192x256W4 = {192, 256, 64, 8.0, 0.45};
+// packed int4 weights: the in-register unpack makes a stage longer where few
+// blocks run and matters less where the chip is full; 192x256 runs four waves
+// on 64-deep stages
+constexpr TileModel kTilesW4[] = {
+    {256, 128, 128, 6.4, 0.636, 0.3},
+    {128, 128, 128, 4.8, 0.416, 0.3},
+    {192, 256, 64, 10.2, 0.569, 0.3},
+    {64, 64, 128, 2.8, 0.254, 0.5, 2},
+    {256, 256, 128, 8.2, 1.023, 0.6},
+    {64, 128, 128, 3.6, 0.280, 0.0},
+};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 static_assert(kNumTiles == MQ_PREFILL_TILES, "one explicit path per tile");
 static_assert(kTiles[kTile256x128].tn == T256x128<8, 8>::TN &&
@@ -1281,10 +1306,12 @@ static_assert(kTiles[kTile256x128].tn == T256x128<8, 8>::TN &&
                   kTiles[kTile64x64].tm == T64x64<8, 8>::TM &&
                   kTiles[kTile256x256W8].tn == T256x256W8<8, 8>::TN &&
                   kTiles[kTile256x256W8].bk == T256x256W8<8, 8>::BK &&
-                  kTiles[kTile128x64].tm == T128x64<8, 8>::TM &&
-                  kTiles[kTile128x64].tn == T128x64<8, 8>::TN,
+                  kTiles[kTile64x128].tm == T64x128<8, 8>::TM &&
+                  kTiles[kTile64x128].tn == T64x128<8, 8>::TN &&
+                  sizeof(kTilesW4) == sizeof(kTiles) &&
+                  kTilesW4[kTile192x256].bk == T192x256<4, 8>::BK,
               "the time model's rows follow the tile indices");
-constexpr double kBusySlowdown = 0.60;
+constexpr int kCUs = 256;
 // The same for the 16-bit tiles, whose work-groups per CU (occ) share its
 // rate: a CU with n tiles takes ceil(n / occ) fixed parts and n times the
 // stages, a stage stage_us * (1 + busy * (busy fraction of the CUs)^2).
@@ -1307,16 +1334,17 @@ static_assert(kTilesA16[kA16T64x128].tn == T64x128A16<8>::TN &&
                   T64x128A16<8>::GROUPS_PER_CU == 2 && T128x128A16<8>::GROUPS_PER_CU == 2 &&
                   T128x192A16<8>::GROUPS_PER_CU == 1,
               "the 16-bit time model's rows follow the tiles");
-// int4 weights: the in-register unpack makes a K-loop stage ~1.35x longer
-constexpr double kInt4StageFactor = 1.35;
 // A K split adds round trips to memory (partial stores, the counter, the
 // partial loads) and moves every slice's int32 tile through memory and back
-// (written through, read around the caches): fitted, 5.2 us plus 0.24 us
+// (written through, read around the caches): fitted, 2.5 us plus 0.24 us
 // per MB of partial sums stored and loaded.
-constexpr double kSplitFixedUs = 5.2;
+constexpr double kSplitFixedUs = 2.5;
 constexpr double kSplitUsPerMB = 0.24;
-constexpr int kCUs = 256;
 constexpr int kMaxSplits = 8;
+// 32 MiB of partial sums (~16 us of traffic) is
+// what the scratch array of mq_qlinear_noalloc holds: larger splits won only
+// above K = 25000, by less than 15% in the model
+constexpr int64_t kMaxSplitBytes = 32 << 20;
 
 struct Choice {
     int tile, splits;
@@ -1332,33 +1360,33 @@ Choice choose(const QLinearArgs& p, bool can_split, const int64_t* Ns = nullptr,
     const int only = p.force_tile >= 0 && p.force_tile < kNumTiles ? p.force_tile : -1;
     for (int c = 0; c < kNumTiles; ++c) {
         if (only >= 0 && c != only) continue;
-        // the 128x64 tile (below) only where it was measured ahead
-        if (c == kTile128x64 && only < 0 && (p.w_bits != 8 || p.K < 4096)) continue;
-        const TileModel& t = c == kTile192x256 && p.w_bits == 4 ? kTile192x256W4 : kTiles[c];
+        const TileModel& t = (p.w_bits == 4 ? kTilesW4 : kTiles)[c];
         int64_t cols = 0;
         for (int i = 0; i < nN; ++i) cols += ((Ns ? Ns[i] : p.N) + t.tn - 1) / t.tn;
         const int64_t tiles = ((p.M + t.tm - 1) / t.tm) * cols;
-        // ... and with a tile for every CU (with fewer, 64x64 at one
-        // work-group per CU is ahead: 512 x 16384 -> 2048 28.2 against
-        // 36.9 us, which the 64x64 row of the model does not capture)
-        if (c == kTile128x64 && only < 0 && tiles < kCUs) continue;
         const int64_t kt = (p.K + t.bk - 1) / t.bk;
         const int64_t slots = (int64_t)kCUs * t.occ;
-        for (int sp = 1; sp <= (can_split && t.splits ? kMaxSplits : 1); sp *= 2) {
+        for (int sp = 1; sp <= (can_split ? kMaxSplits : 1); sp *= 2) {
             const int64_t per = (kt + sp - 1) / sp;
-            if (sp > 1 && per < 4) break;  // slices too thin to pipeline
+            // slices too thin to pipeline, more counters than their area holds,
+            // or more partial sums than kMaxSplitBytes
+            if (sp > 1 && (per < 4 || tiles > kMaxSplitTiles ||
+                           tiles * sp * t.tm * t.tn * 4 > kMaxSplitBytes))
+                break;
             const int64_t items = tiles * sp;
-            const int64_t rounds = (items + slots - 1) / slots;
-            const double busy = (double)(items < slots ? items : slots) / (double)slots;
-            const double stage = t.stage_us * (p.w_bits == 4 ? kInt4StageFactor : 1.0) *
-                                 (1.0 + kBusySlowdown * busy);
-            const double t_blk = t.fixed_us + stage * (double)per;
+            // whole rounds, then the remaining blocks on a chip partly busy
+            const int64_t full = items / slots, rest = items % slots;
+            const double busy = (double)rest / (double)slots;
+            auto round_us = [&](double b) {
+                return t.fixed_us + t.stage_us * (1.0 + t.busy * b * b) * (double)per;
+            };
             const double exchange =
                 sp > 1 ? kSplitFixedUs + kSplitUsPerMB * (double)tiles * (2 * sp - 1) * t.tm *
                                              t.tn * 4 * 1e-6
                        : 0.0;
-            const double tt = (double)rounds * t_blk + exchange;
-            if (tt < best_t * 0.97) {  // a split has to win clearly
+            const double tt = (double)full * round_us(1.0) + (rest ? round_us(busy) : 0.0) +
+                              exchange;
+            if (tt < best_t * (sp > 1 ? 0.97 : 1.0)) {  // a split has to win clearly
                 best_t = tt;
                 best = {c, sp};
             }
@@ -1405,7 +1433,7 @@ hipError_t launch_a(const QLinearArgs& p, hipStream_t s)
     case kTile192x256: return launch_cfg<T192x256<WB, OB>, ASYM>(p, ch.splits, s);
     case kTile64x64: return launch_cfg<T64x64<WB, OB>, ASYM>(p, ch.splits, s);
     case kTile256x256W8: return launch_cfg<T256x256W8<WB, OB>, ASYM>(p, ch.splits, s);
-    case kTile128x64: return launch_cfg<T128x64<WB, OB>, ASYM>(p, ch.splits, s);
+    case kTile64x128: return launch_cfg<T64x128<WB, OB>, ASYM>(p, ch.splits, s);
     default: return launch_cfg<T128x128<WB, OB>, ASYM>(p, ch.splits, s);
     }
 }
@@ -1427,7 +1455,7 @@ hipError_t launch_group_a(const QLinearArgs& p, const GroupArgs& g, hipStream_t 
     case kTile192x256: return launch_group_cfg<T192x256<WB, OB>, ASYM>(p, g, s);
     case kTile64x64: return launch_group_cfg<T64x64<WB, OB>, ASYM>(p, g, s);
     case kTile256x256W8: return launch_group_cfg<T256x256W8<WB, OB>, ASYM>(p, g, s);
-    case kTile128x64: return launch_group_cfg<T128x64<WB, OB>, ASYM>(p, g, s);
+    case kTile64x128: return launch_group_cfg<T64x128<WB, OB>, ASYM>(p, g, s);
     default: return launch_group_cfg<T128x128<WB, OB>, ASYM>(p, g, s);
     }
 }

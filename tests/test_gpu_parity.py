@@ -156,6 +156,31 @@ def test_split_k_parity(case, tile):
     assert np.array_equal(gpu_layer(ld, path=path).y_q, o.y_q)
 
 
+@pytest.mark.parametrize("tile", [0, 5])
+@pytest.mark.parametrize("case", SPLIT_CASES, ids=lambda c: "x".join(map(str, c[:5])))
+def test_split_k_parity_256x128_64x128(case, tile):
+    """The same on the 256x128 and the 64x128 tile."""
+    test_split_k_parity(case, tile)
+
+
+@pytest.mark.parametrize("first", [0, 1, 3, 5])
+def test_split_workspace_shared_by_layers_of_different_sizes(first):
+    """One workspace for a split layer of a few tiles and then one of more
+    than 64 (whose counters reach past the first's): the first's partial sums
+    must not be read as the second's counters, whatever tile the first ran."""
+    mq, torch = _mq(), _torch()
+    small = wl.make_layer("share", wl.Layer("x", 130, 8192, 300, w_bits=8, out_bits=16))
+    big = wl.make_layer("share", wl.Layer("x", 200, 12288, 1284, w_bits=8, out_bits=16))
+    nbytes, _ = split_workspace_bound(257, 1284, 0)
+    ws = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+    o_small, o_big = oracle_layer(small), oracle_layer(big)
+    many = mq.prefill_tile_path(3)  # 4 * 21 tiles
+    for _ in range(2):
+        assert_same(gpu_layer(small, workspace=ws, path=mq.prefill_tile_path(first)), o_small)
+        assert int(ws[:4096].count_nonzero()) == 0, "partial sums left in the counter area"
+        assert_same(gpu_layer(big, workspace=ws, path=many), o_big)
+
+
 MANY_TILE_CASES = [
     # M, K, N, w_bits, out_bits, bias, asym: more 256x256 output tiles than
     # the chip has CUs (two to three rounds of work-groups), ragged M and N

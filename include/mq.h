@@ -209,7 +209,9 @@ int64_t mq_qlinear_workspace_bytes(int64_t M, int64_t K, int64_t N, int32_t w_bi
  * added exactly before the requant.
  *   workspace        device memory owned by the caller, 256-byte aligned,
  *                    zero-filled once before its first use with this
- *                    library; every call leaves its counters at zero again.
+ *                    library; every call leaves its counters at zero again,
+ *                    so layers of different sizes may use it one after
+ *                    another.
  *                    NULL (or workspace_bytes below
  *                    mq_qlinear_workspace_bytes) -> no split.  Calls that may
  *                    run concurrently must not share a workspace.

@@ -234,8 +234,9 @@ mq_status mq_qlinear_ws(const int8_t* a_q, int64_t M, int64_t K, int64_t N,
  * K split runs here too, with its workspace in a static device array of
  * MQ_NOALLOC_SCRATCH_BYTES on each GPU (held from the library's load until
  * the process ends; the first call on a device looks up that device's copy).
- *   Returns MQ_ERR_UNSUPPORTED, launching nothing, when the shape's K split
- *   needs more than MQ_NOALLOC_SCRATCH_BYTES; other errors as mq_qlinear.
+ *   No K split needs more than MQ_NOALLOC_SCRATCH_BYTES (counters and partial
+ *   sums together), so every shape mq_qlinear takes is taken; errors as
+ *   mq_qlinear.
  *   Each call clears the arrival counters it uses with a fill kernel on
  *   `stream` (no memset node, so the call can be captured).  All calls on
  *   one GPU share that GPU's array and it keeps the last call's contents:

@@ -61,7 +61,7 @@ extern "C" mq_status mq_qlinear_noalloc(const int8_t* a_q, int64_t M, int64_t K,
     if (st != MQ_OK || M == 0 || N == 0) return st;
     const int64_t need = mq_qlinear_workspace_bytes(M, K, N, w_bits, out_bits);
     if (need < 0) return MQ_ERR_INVALID_ARG;
-    if (need > kScratchBytes) return MQ_ERR_UNSUPPORTED;  // the split would not fit
+    if (need > kScratchBytes) return MQ_ERR_UNSUPPORTED;  // (the K split is chosen to fit)
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (need > 0) {
         int dev = -1;

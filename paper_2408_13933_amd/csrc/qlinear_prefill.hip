@@ -1341,10 +1341,10 @@ static_assert(kTilesA16[kA16T64x128].tn == T64x128A16<8>::TN &&
 constexpr double kSplitFixedUs = 2.5;
 constexpr double kSplitUsPerMB = 0.24;
 constexpr int kMaxSplits = 8;
-// 32 MiB of partial sums (~16 us of traffic) is
-// what the scratch array of mq_qlinear_noalloc holds: larger splits won only
-// above K = 25000, by less than 15% in the model
-constexpr int64_t kMaxSplitBytes = 32 << 20;
+// Counters and partial sums fit the scratch array of mq_qlinear_noalloc
+// (32 MiB, ~16 us of traffic), so that entry point refuses no shape: larger
+// splits won only above K = 25000, by less than 15% in the model
+constexpr int64_t kMaxSplitBytes = MQ_NOALLOC_SCRATCH_BYTES;
 
 struct Choice {
     int tile, splits;
@@ -1369,9 +1369,10 @@ Choice choose(const QLinearArgs& p, bool can_split, const int64_t* Ns = nullptr,
         for (int sp = 1; sp <= (can_split ? kMaxSplits : 1); sp *= 2) {
             const int64_t per = (kt + sp - 1) / sp;
             // slices too thin to pipeline, more counters than their area holds,
-            // or more partial sums than kMaxSplitBytes
+            // or a workspace beyond kMaxSplitBytes
             if (sp > 1 && (per < 4 || tiles > kMaxSplitTiles ||
-                           tiles * sp * t.tm * t.tn * 4 > kMaxSplitBytes))
+                           split_counter_bytes(tiles) + tiles * sp * t.tm * t.tn * 4 >
+                               kMaxSplitBytes))
                 break;
             const int64_t items = tiles * sp;
             // whole rounds, then the remaining blocks on a chip partly busy

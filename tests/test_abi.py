@@ -5,6 +5,7 @@ device.  The Eq.(2)-(3) host arithmetic is compared with the oracle here too.
 import ctypes
 import math
 import os
+import random
 import re
 
 import numpy as np
@@ -166,13 +167,29 @@ def test_qlinear_noalloc_rejects_invalid_arguments(kw):
     assert qlin_noalloc(**kw) == 1
 
 
-def test_qlinear_noalloc_rejects_split_beyond_its_array():
-    # the K split of this shape needs more than MQ_NOALLOC_SCRATCH_BYTES:
-    # refused on the host before any device work
-    need = mq.mq_qlinear_workspace_bytes(1024, 65536, 2048, 8, 16)
-    assert need > mq.NOALLOC_SCRATCH_BYTES
-    assert qlin_noalloc(M=1024, K=65536, N=2048, out_bits=16) == 2
-    # nothing to do: no device work either
+@pytest.mark.parametrize("M,K,N,w_bits", [
+    # splits whose partial sums alone would fill the array of 32 MiB
+    (512, 24576, 8192, 8), (400, 22016, 8192, 8), (256, 49152, 4096, 8), (1024, 20480, 4096, 8),
+    (1024, 65536, 2048, 8), (512, 16384, 8192, 4), (1024, 16384, 4096, 4),
+])
+def test_qlinear_noalloc_split_fits_its_array(M, K, N, w_bits):
+    # counters and partial sums together: no shape is refused
+    for out_bits in (8, 16):
+        need = mq.mq_qlinear_workspace_bytes(M, K, N, w_bits, out_bits)
+        assert 0 <= need <= mq.NOALLOC_SCRATCH_BYTES
+
+
+def test_qlinear_noalloc_split_fits_its_array_over_shapes():
+    rng = random.Random(5)
+    size = lambda lo, hi: int(math.exp(rng.uniform(math.log(lo), math.log(hi))))
+    split = 0
+    for _ in range(20000):
+        M, K, N = size(17, 4096), size(1, 1024) * 64, size(16, 1 << 18)
+        need = mq.mq_qlinear_workspace_bytes(M, K, N, rng.choice((4, 8)), 8)
+        assert 0 <= need <= mq.NOALLOC_SCRATCH_BYTES, (M, K, N)
+        split += need > 0
+    assert split > 1000
+    # nothing to do: no device work
     assert qlin_noalloc(M=0) == 0 and qlin_noalloc(N=0) == 0
 
 

@@ -69,21 +69,29 @@ def test_noalloc_matches_workspace_entry_point():
     assert np.array_equal(y.cpu().numpy(), o.y_q)
 
 
-def test_noalloc_rejects_split_beyond_scratch():
-    """A shape whose K split needs more than the static array returns
-    MQ_ERR_UNSUPPORTED and writes nothing."""
+@pytest.mark.parametrize("M,K,N,w_bits", [(512, 16384, 8192, 4), (256, 49152, 4096, 8)])
+def test_noalloc_takes_the_largest_splits(M, K, N, w_bits):
+    """Shapes whose best split by partial sums alone is exactly the static
+    array (the counters come on top): taken, with the bits of the workspace
+    entry point, four sampled token rows with those of the generic kernel."""
     import torch
 
     import paper_2408_13933_amd as mq
 
-    M, K, N = 1024, 65536, 2048
-    assert mq.mq_qlinear_workspace_bytes(M, K, N, 8, 16) > mq.NOALLOC_SCRATCH_BYTES
-    a = torch.zeros((M, K), dtype=torch.int8, device="cuda")
-    w = torch.zeros((N, K), dtype=torch.int8, device="cuda")
-    s = torch.ones(N, device="cuda")
-    c = torch.zeros(N, dtype=torch.int32, device="cuda")
-    y = torch.full((M, N), 5, dtype=torch.int16, device="cuda")
-    with pytest.raises(mq.MQError):
-        mq.mq_qlinear_noalloc(a, w, 8, s, c, 0.1, 0, 0.1, 0, 16, out=y)
-    torch.cuda.synchronize()
-    assert bool((y == 5).all())
+    need = mq.mq_qlinear_workspace_bytes(M, K, N, w_bits, 16)
+    assert need <= mq.NOALLOC_SCRATCH_BYTES
+    g = torch.Generator(device="cuda").manual_seed(K)
+    a = torch.randint(-128, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    w = torch.randn(N, K, generator=g, device="cuda") * 0.02
+    wq, ws, cs = mq.mq_pack_weights(w, w_bits)
+    del w
+    args = (wq, w_bits, ws, cs, 0.02, 3, 2e-3, -5, 16)
+    work = torch.zeros(max(need, 256), dtype=torch.uint8, device="cuda")
+    ref = mq.mq_qlinear(a, *args, workspace=work)
+    y = torch.full((M, N), 77, dtype=torch.int16, device="cuda")
+    mq.mq_qlinear_noalloc(a, *args, out=y)
+    assert torch.equal(y, ref)
+    rows = [0, 1, M // 2, M - 1]
+    got = mq.mq_qlinear(a[rows].contiguous(), *args, path=mq.PATH_GENERIC)
+    assert torch.equal(y[rows], got)
+    assert len(torch.unique(y)) > 1000

@@ -775,12 +775,16 @@ hipError_t launch_attn_t(AttnArgs& p, int32_t H, int32_t G, hipStream_t s)
 
 }  // namespace
 
+// The lane's offset inside a whole tile, 12 rows and less than 64 columns in
+// units of up to two bytes, fits 32 bits (store_row).
+constexpr int64_t kMaxLdy = (0x7FFFFFFF - 64) / 12;
+
 bool attn_direct_supported(int64_t M, int64_t N, int64_t ldy, int32_t H, int32_t G)
 {
-    // 32-bit row and column indices, the lane's byte offset inside a tile,
-    // the flat rows of a group and the work items in range
+    // 32-bit row and column indices, the lane's offset inside a tile, the
+    // flat rows of a group and the work items in range
     const int64_t rb = ((M + 15) / 16) * H;
-    return M <= 0x3FFFFFFF / (H / G) && N <= 0x3FFFFFFF && ldy <= (1 << 28) &&
+    return M <= 0x3FFFFFFF / (H / G) && N <= 0x3FFFFFFF && ldy <= kMaxLdy &&
            rb <= 0x7FFFFFFF / ((N + 31) / 32);
 }
 

@@ -511,3 +511,19 @@ def test_probe_read_validation():
                 dict(unroll=32), dict(sink=None), dict(src=None)):
         assert call(**bad) == mq.MQ_ERR_INVALID_ARG, bad
     assert call(bytes=1 << 40, blocks=1) == mq.MQ_ERR_UNSUPPORTED
+
+
+def test_attn_direct_row_stride_bound():
+    """The one-launch attention kernels form a lane's offset inside a tile (12
+    rows and less than 64 columns of codes of up to two bytes) in 32 bits:
+    every output row stride they accept keeps it there."""
+    f = getattr(mq.lib(), "_ZN2mq21attn_direct_supportedElllii")
+    f.restype = ctypes.c_bool
+    f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int32] * 2
+    lo, hi = 64, 1 << 40
+    assert f(16, 32, lo, 1, 1) and not f(16, 32, hi, 1, 1)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if f(16, 32, mid, 1, 1) else (lo, mid)
+    assert 12 * lo + 64 <= 2 ** 31 - 1 and (12 * lo + 64) * 2 <= 2 ** 32 - 1
+    assert lo > 1 << 27                          # and no shorter than it has to be

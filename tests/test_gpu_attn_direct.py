@@ -95,3 +95,23 @@ def test_transpose_edges(rows, cols, ldx):
     x = np.random.default_rng(rows + cols).integers(-128, 128, (rows, ldx)).astype(np.int8)
     y = mq.mq_transpose_i8(torch.from_numpy(x).cuda()[:, :cols])
     assert np.array_equal(y.cpu().numpy(), x[:, :cols].T)
+
+
+# a lane's byte offset inside a 16 x 32 tile is 12 rows and 30 codes at most,
+# in 32 bits: the longest output row below 2^32 bytes for 16-bit codes, and
+# rows beyond it
+@pytest.mark.parametrize("ldy", [178956960, 178956976, 1 << 28])
+def test_direct_long_output_rows(ldy):
+    import paper_2408_13933_amd as mq
+    import torch
+    rng = np.random.default_rng(5)
+    H, M, N, K = 1, 16, 32, 64
+    a = rng.integers(-32768, 32768, (H, M, K)).astype(np.int16)
+    b = rng.integers(-128, 128, (1, N, K)).astype(np.int8)
+    prm = (3e-5, 7, 0.02, -3, 1e-2, 5, 16)
+    ref = oracle.attn_matmul(a, b, *prm)
+    buf = torch.empty((M - 1) * ldy + N, dtype=torch.int16, device="cuda")
+    y = buf.as_strided((H, M, N), (M * ldy, ldy, 1))
+    y.zero_()
+    mq.mq_attn_matmul(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda(), *prm, out=y)
+    assert np.array_equal(y.cpu().numpy(), ref)

@@ -1211,11 +1211,11 @@ hipError_t launch_rope_apply(const int16_t* x, int64_t T, int64_t H, int64_t D, 
     const int64_t half = D / 2;
     if (T == 0) return hipSuccess;
     if (H * half > 0x7FFFFFFF - 256) return hipErrorInvalidValue;
-    // whole aligned groups of eight in both halves and in the output, and
-    // enough of them to fill the chip (1024 tokens x 4 heads of 64: 2.6 us
-    // with one pair per thread, 3.0 with eight)
+    // whole aligned groups of eight in both halves and in the output, with
+    // the last block's pair index in 32 bits
     const uintptr_t yal = bits == 8 ? 8 : 16;
-    const bool vec = half % 8 == 0 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)y % yal) == 0;
+    const bool vec = half % 8 == 0 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)y % yal) == 0 &&
+                     H * half <= 0x7FFFFFFF - 8 * 256;
     const int64_t threads = H * half / (vec ? 8 : 1);
     const dim3 g((unsigned)((threads + 255) / 256), (unsigned)(T < 65535 ? T : 65535));
     const int32_t h32 = (int32_t)H, hf = (int32_t)half;

@@ -343,3 +343,28 @@ def test_lut_mul_table_in_memory_and_in_lds(n):
     ref = oracle.mul_requant(lut[x1.astype(np.int64) + 32768], 9e-5, -3, x2, 1.6e-4, 7, 0.067, 3, 8)
     y = mq.mq_lut_mul(_dev(x1), _dev(lut), 9e-5, -3, _dev(x2), 1.6e-4, 7, 0.067, 3, 8)
     assert np.array_equal(y.cpu().numpy(), ref)
+
+
+# pairs per token at the top of the 32-bit index: the last count of eight-pair
+# threads whose last block ends inside it, and the last count accepted
+@pytest.mark.parametrize("pairs", [2 ** 31 - 2056, 2 ** 31 - 264])
+def test_rope_pair_index_range(pairs):
+    import torch
+    mq = _mq()
+    D = 16
+    H = pairs // (D // 2)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.empty((1, H * D), dtype=torch.int16, device="cuda")
+    n = 1 << 20
+    x.view(-1)[:H * D // n * n].view(-1, n)[:] = torch.randint(-30000, 30000, (n,), generator=g,
+                                                               device="cuda").to(torch.int16)
+    x[0, -4096 * D:] = torch.randint(-30000, 30000, (4096 * D,), generator=g,
+                                     device="cuda").to(torch.int16)
+    table = mq.mq_rope_table(1, D, pos0=77)
+    y = torch.zeros((1, H * D), dtype=torch.int8, device="cuda")
+    mq.mq_rope_apply(x, H, 2e-4, -7, 0.05, -2, table, 8, out=y)
+    for lo in (0, H // 2, H - 4096):
+        part = slice(lo * D, (lo + 4096) * D)
+        ref = mq.mq_rope_apply(x[:, part].contiguous(), 4096, 2e-4, -7, 0.05, -2, table, 8)
+        assert torch.equal(y[:, part], ref)
+        assert len(torch.unique(ref)) > 100

@@ -62,9 +62,9 @@ __global__ __launch_bounds__(kThreads) void arl_forward_kernel(const float* __re
     for (int64_t i = begin + t0; i < n; i += stride) y[i] = arl_y(x[i], alpha, beta, q_max);
 }
 
-// One element's input gradient and its terms of the two sums.  gb sums the
-// gradients outside the range; the scale alpha multiplies the whole sum (the
-// definition's terms are g * alpha, exact products in fp64).
+// One element's input gradient and its terms of the two sums.  gb sums
+// g * (1 - mask), so that an infinite or NaN gradient shows in it inside the
+// range too; the scale alpha multiplies the whole sum.
 __device__ inline float arl_grad(float xi, float gi, float alpha, float beta, float q_max,
                                  double& ga, double& gb)
 {
@@ -75,7 +75,7 @@ __device__ inline float arl_grad(float xi, float gi, float alpha, float beta, fl
     const bool in = u >= 0.0f && u <= q_max;
     const double g = (double)gi;
     ga += g * ((double)c + (double)beta - (in ? (double)t : 0.0));
-    gb += in ? 0.0 : g;
+    gb += g * (in ? 0.0 : 1.0);
     return in ? gi : 0.0f;
 }
 

@@ -78,6 +78,27 @@ def test_arl_forward_backward_parity(n, offset, params):
     assert grads2[:2].cpu().numpy().tolist() == [ga, gb]
 
 
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("at", [0, 7, 998])  # four at a time, and the last elements
+@pytest.mark.parametrize("inside", [True, False])
+def test_arl_backward_nonfinite_gradient(bad, at, inside):
+    """One infinite or NaN gradient, inside the range or clipped, shows in
+    both sums as in the definition (g alpha 0 inside the range is NaN)."""
+    mq = _mq()
+    rng = np.random.default_rng(9)
+    x = rng.uniform(-3, 3, 999).astype(np.float32)
+    g = rng.standard_normal(999).astype(np.float32)
+    x[at] = 1.0 if inside else 1e4
+    g[at] = bad
+    gx, grads = mq.mq_arl_backward(_dev(x), _dev(g), 0.5, -130.0, 8)
+    with np.errstate(invalid="ignore"):
+        o_gx, o_ga, o_gb = oracle.arl_backward(x, g, 0.5, -130.0, 8)
+    assert np.array_equal(gx.cpu().numpy(), o_gx, equal_nan=True)
+    got = grads[:2].cpu().numpy()
+    assert not np.isfinite(o_ga) and not np.isfinite(o_gb)
+    assert np.array_equal(got, [o_ga, o_gb], equal_nan=True)
+
+
 def test_arl_in_place_and_empty():
     mq, torch = _mq(), _torch()
     x, _ = _arl_inputs(5000, 3)

@@ -79,35 +79,37 @@ __device__ inline float arl_grad(float xi, float gi, float alpha, float beta, fl
     return in ? gi : 0.0f;
 }
 
-// n4 groups of four through 16-byte loads, two groups in flight per thread,
-// elements [begin, n) one by one.  Bound by memory (12 bytes per element):
-// 2048 x 2048 took 12.0 us with four-byte accesses, 9.9 this way.
+// n4 groups of four through 16-byte loads at any alignment (so which thread sums
+// which elements depends on n alone), two groups in flight per thread, elements
+// [4 n4, n) one by one.  Bound by memory (12 bytes per element): 2048 x 2048
+// took 12.0 us with four-byte accesses, 9.9 this way.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(kThreads) void arl_backward_kernel(
-    const float* __restrict__ x, const float* __restrict__ g, int64_t n4, int64_t begin, int64_t n,
-    float alpha, float beta, float q_max, float* __restrict__ gx, double* __restrict__ partials)
+    const float* __restrict__ x, const float* __restrict__ g, int64_t n4, int64_t n, float alpha,
+    float beta, float q_max, float* __restrict__ gx, double* __restrict__ partials)
 {
 #pragma clang fp contract(off)
     __shared__ double red[2][kThreads / 64];
     double ga = 0.0, gb = 0.0;
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     const int64_t t0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const float4* x4 = reinterpret_cast<const float4*>(x);
-    const float4* g4 = reinterpret_cast<const float4*>(g);
-    float4* o4 = reinterpret_cast<float4*>(gx);
-    auto four = [&](const float4 a, const float4 b) {
-        return make_float4(arl_grad(a.x, b.x, alpha, beta, q_max, ga, gb),
-                           arl_grad(a.y, b.y, alpha, beta, q_max, ga, gb),
-                           arl_grad(a.z, b.z, alpha, beta, q_max, ga, gb),
-                           arl_grad(a.w, b.w, alpha, beta, q_max, ga, gb));
+    const f32x4_any* x4 = reinterpret_cast<const f32x4_any*>(x);
+    const f32x4_any* g4 = reinterpret_cast<const f32x4_any*>(g);
+    f32x4_any* o4 = reinterpret_cast<f32x4_any*>(gx);
+    auto four = [&](const f32x4_any a, const f32x4_any b) {
+        f32x4_any r;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] = arl_grad(a[k], b[k], alpha, beta, q_max, ga, gb);
+        return r;
     };
     int64_t i = t0;
     for (; i + stride < n4; i += 2 * stride) {
-        const float4 a0 = x4[i], b0 = g4[i], a1 = x4[i + stride], b1 = g4[i + stride];
+        const f32x4_any a0 = x4[i], b0 = g4[i], a1 = x4[i + stride], b1 = g4[i + stride];
         o4[i] = four(a0, b0);
         o4[i + stride] = four(a1, b1);
     }
     if (i < n4) o4[i] = four(x4[i], g4[i]);
-    for (i = begin + t0; i < n; i += stride)
+    for (i = 4 * n4 + t0; i < n; i += stride)
         gx[i] = arl_grad(x[i], g[i], alpha, beta, q_max, ga, gb);
     for (int o = 32; o > 0; o >>= 1) {
         ga += __shfl_xor(ga, o);
@@ -287,12 +289,9 @@ hipError_t launch_arl_backward(const float* x, const float* g, int64_t n, float 
                                hipStream_t st)
 {
     const float q_max = (float)((1 << bits) - 1);
-    const bool vec = ((uintptr_t)x % 16) == 0 && ((uintptr_t)g % 16) == 0 &&
-                     ((uintptr_t)gx % 16) == 0;
-    const int64_t n4 = vec ? n / 4 : 0;
     const int blocks = grid_for(n, kThreads * 4, max_partials);
     double* partials = grads + 2;
-    arl_backward_kernel<<<blocks, kThreads, 0, st>>>(x, g, n4, n4 * 4, n, alpha, beta, q_max, gx,
+    arl_backward_kernel<<<blocks, kThreads, 0, st>>>(x, g, n / 4, n, alpha, beta, q_max, gx,
                                                      partials);
     arl_reduce_kernel<<<1, kReduceThreads, 0, st>>>(partials, blocks, grads);
     return hipGetLastError();

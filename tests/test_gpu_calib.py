@@ -99,6 +99,20 @@ def test_arl_backward_nonfinite_gradient(bad, at, inside):
     assert np.array_equal(got, [o_ga, o_gb], equal_nan=True)
 
 
+@pytest.mark.parametrize("n", [3, 4099, 2 ** 21 + 1])
+def test_arl_backward_sums_do_not_depend_on_alignment(n):
+    """The same values summed from buffers that start at any element."""
+    mq, torch = _mq(), _torch()
+    x, g = _arl_inputs(n, n)
+    want = None
+    for ox, og, oy in ((0, 0, 0), (1, 0, 0), (0, 2, 0), (0, 0, 3), (3, 1, 2)):
+        gx = torch.empty(n + 3, device="cuda")[oy:oy + n]
+        gx, grads = mq.mq_arl_backward(_dev(x, ox), _dev(g, og), 0.02, -127.3, 8, gx=gx)
+        got = (grads[:2].cpu().numpy().tobytes(), gx.cpu().numpy().tobytes())
+        want = want or got
+        assert got == want, (ox, og, oy)
+
+
 def test_arl_in_place_and_empty():
     mq, torch = _mq(), _torch()
     x, _ = _arl_inputs(5000, 3)

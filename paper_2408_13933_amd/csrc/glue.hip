@@ -527,10 +527,12 @@ __device__ inline int64_t causal_keys(int64_t m, int64_t K, int64_t period, int6
 //   exp(-alpha d) = exp(-256 alpha h) exp(-alpha l).
 // Each block evaluates the two 256-entry factor tables once (one exp per
 // entry, in LDS); a key then costs two table reads and one fp64 product,
-// within three ulp of the direct exp.  The code is rint(e * s) + zy with
-// s = (1 / sum) (1 / ay) (two roundings where the oracle divides twice);
-// the codes can differ from the oracle's only where the fp64 value sits
-// within a few ulp of a rounding tie.  Hidden keys are written as zy.
+// within three ulp of the direct exp, and its quotient is e * s with s =
+// (1 / sum) (1 / ay): within 2^-47 of the definition's e / sum / ay, its exps
+// and sum in another order included.  Up to 2^17 that is 2^-30; a row with a
+// quotient within 2^-29 of a half-integer is evaluated again as it is defined
+// (exact_codes), so no code depends on the tables.  Hidden keys are written
+// as zy.
 // Each wave takes kSmRows rows in snake order (m, 2G - 1 - m, ... for G waves
 // in the grid): under a causal mask whose period divides 2G
 // the key counts of each pair sum to the period plus one.
@@ -615,16 +617,27 @@ struct ExpTables {
     }
 };
 
-// rint(e s) + zy, not yet clamped.  Adding 1.5 * 2^52 rounds t in [0, 2^31)
-// to an integer (to nearest, ties to even) held in the low word; CLAMP caps
-// t when s (an upper bound of t, e <= 1) exceeds 1e9.
-template <bool CLAMP>
-__device__ inline int32_t requant_prob(double e, double s, int32_t zy)
+// t + zy to the nearest integer, not yet clamped to the output range.
+// EXACT: for t in [0, 2^17]; adding 1.5 * 2^20 leaves the integer part of t in
+// the high word and its fraction, to 2^-32, in the low one, and near becomes
+// the least of the fractions' distances above kTieLow, at most kTieSpan for one
+// within 2^-29 of a half.  Otherwise 1.5 * 2^52 rounds t in [0, 2^31) to an
+// integer (ties to even) in the low word.  CLAMP caps t where it may be
+// larger (s is; e <= 1).
+constexpr double kSplitShift = 1572864.0;   // 1.5 * 2^20
+constexpr int32_t kSplitHigh = 0x41380000;  // its high word
+constexpr uint32_t kTieLow = 0x80000000u - 8, kTieSpan = 16;
+template <bool CLAMP, bool EXACT>
+__device__ inline int32_t requant_prob(double e, double s, int32_t zy, uint32_t& near)
 {
 #pragma clang fp contract(off)
     double t = e * s;
-    if (CLAMP) t = fmin(t, 1e9);
-    return rint_low(t + kRintShift) + zy;
+    if (CLAMP) t = fmin(t, 131072.0);
+    if constexpr (!EXACT) return rint_low(t + kRintShift) + zy;
+    const uint64_t b = (uint64_t)__double_as_longlong(t + kSplitShift);
+    const uint32_t frac = (uint32_t)b;
+    near = min(near, frac - kTieLow);
+    return (int32_t)(b >> 32) + (int32_t)(frac >> 31) + (zy - kSplitHigh);
 }
 
 // A wave's part of one row: chunk c < NCA is the 256 keys from first + step c
@@ -689,23 +702,57 @@ struct RowPart {
         }
         return sum;
     }
-    // rint(e s) + zy of every key (hidden keys: rint(0) + zy)
-    template <int BITS, bool CLAMP>
-    __device__ __forceinline__ void codes(int K, double s, int32_t zy, void* y, int64_t base,
-                                          int first, int step) const
+    // e s + zy of every key, rounded (hidden keys: zy); whether one of the
+    // wave's lies near a tie
+    template <bool CLAMP, bool EXACT>
+    __device__ __forceinline__ bool codes(double s, int32_t zy, int32_t (&o)[NCA][4]) const
+    {
+        uint32_t near = 0xFFFFFFFFu;
+#pragma unroll
+        for (int c = 0; c < NCA; ++c)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                o[c][u] = requant_prob<CLAMP, EXACT>(e[c][u], s, zy, near);
+        return EXACT && __ballot(near <= kTieSpan) != 0;
+    }
+    template <int BITS>
+    __device__ __forceinline__ static void store(const int32_t (&o)[NCA][4], int K, void* y,
+                                                 int64_t base, int first, int step)
     {
         const int k = 4 * (threadIdx.x & 63);
 #pragma unroll
         for (int c = 0; c < NCA; ++c) {
             const int f = first + step * c;
-            int32_t o[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) o[u] = requant_prob<CLAMP>(e[c][u], s, zy);
-            if (c + 1 < NCA || f + kChunk <= K) store4_any<BITS>(y, base + f + k, o, 4);
-            else if (f + k < K) store4_any<BITS>(y, base + f + k, o, K - f - k);
+            if (c + 1 < NCA || f + kChunk <= K) store4_any<BITS>(y, base + f + k, o[c], 4);
+            else if (f + k < K) store4_any<BITS>(y, base + f + k, o[c], K - f - k);
         }
     }
 };
+
+// The definition, key by key: keys t, t + step, ... of the row (the sum over
+// them, then the codes of those below `end`, hidden ones zy).
+__device__ __forceinline__ double exact_sum(const int16_t* row, int n, int32_t mx, double a, int t,
+                                            int step)
+{
+#pragma clang fp contract(off)
+    double sum = 0.0;
+#pragma unroll 1
+    for (int k = t; k < n; k += step) sum += exp(a * (double)((int32_t)row[k] - mx));
+    return sum;
+}
+template <int BITS>
+__device__ __forceinline__ void exact_codes(const int16_t* row, int n, int end, int32_t mx,
+                                            double a, double sum, double ay, int32_t zy, void* y,
+                                            int64_t base, int t, int step)
+{
+#pragma clang fp contract(off)
+#pragma unroll 1
+    for (int k = t; k < end; k += step) {
+        int32_t q = zy;
+        if (k < n) q = requant_f64<BITS>(exp(a * (double)((int32_t)row[k] - mx)) / sum, ay, zy);
+        store_code<BITS>(y, base + k, q);
+    }
+}
 
 // the wave's chunks past the boundary: probability 0
 template <int BITS>
@@ -720,15 +767,17 @@ __device__ __forceinline__ void hidden_codes(int K, int32_t zy, void* y, int64_t
     }
 }
 
-// CLAMP: 1 / ay > 1e9 (quotients beyond the rounding shift's range).
+// CLAMP: 1 / ay > 2^17.
 // Loads and stores take rows of any length and alignment.
 // Bound by memory at 1024 codes (a plain copy of the 64 MB takes 17.0 us).
 // Measured, 32 heads of causal rows: 1024 codes 23.3 us (27.3 with a branch
-// per chunk of eight codes and four rows per wave), 777 codes 17.9 us (26;
-// 70 on the strided kernel, an exp per key and pass).  Two rows per wave: four
-// took 22.6 and 19.8 us, and 5.9 instead of 5.3 us at 256 tokens.
-template <int BITS, bool CLAMP, int NCA>
-__device__ __forceinline__ void softmax_row(const int16_t* x, int64_t m, int K, int n,
+// per chunk of eight codes and four rows per wave), 777 codes 19.1 us with the
+// tie check, 17.9 without (26; 70 on the strided kernel, an exp per key and
+// pass).  Two rows per wave: four took 22.6 and 19.8 us, and 5.9 instead of
+// 5.3 us at 256 tokens.
+// The row's codes; false, and nothing stored, if one lies near a tie.
+template <int BITS, bool CLAMP, bool EXACT, int NCA>
+__device__ __forceinline__ bool softmax_row(const int16_t* x, int64_t m, int K, int n,
                                             const ExpTables& tab, double ri, int32_t zy, void* y)
 {
 #pragma clang fp contract(off)
@@ -737,12 +786,15 @@ __device__ __forceinline__ void softmax_row(const int16_t* x, int64_t m, int K, 
     const int32_t mx = wave_max_i32(r.max_code(n, 0, kChunk));
     // sum >= 1: the maximum key contributes exp(0)
     const double sum = wave_sum_f64(r.exponentials(n, mx, tab, 0, kChunk));
-    r.template codes<BITS, CLAMP>(K, (1.0 / sum) * ri, zy, y, m * K, 0, kChunk);
+    int32_t o[NCA][4];
+    if (r.template codes<CLAMP, EXACT>((1.0 / sum) * ri, zy, o)) return false;
+    r.template store<BITS>(o, K, y, m * K, 0, kChunk);
+    return true;
 }
 
 // MAXC: chunks of the longest row (4 or 8: with 4 the kernel's registers
 // allow eight waves per SIMD).
-template <int BITS, bool CLAMP, int MAXC>
+template <int BITS, bool CLAMP, bool EXACT, int MAXC>
 __global__ __launch_bounds__(kSmWaves * 64) void softmax_table_kernel(
     const int16_t* __restrict__ x, int64_t M, int64_t K, float ax, float ay, int32_t zy,
     int64_t period, int64_t offset, void* __restrict__ y)
@@ -753,26 +805,52 @@ __global__ __launch_bounds__(kSmWaves * 64) void softmax_table_kernel(
     const int64_t g = (int64_t)blockIdx.x * kSmWaves +
                       __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const double ri = 1.0 / (double)ay;
-#pragma unroll 1
-    for (int r = 0; r < kSmRows; ++r) {
-        const int64_t m = (r & 1) ? (int64_t)(r + 1) * G - 1 - g : (int64_t)r * G + g;
-        if (m >= M) continue;
-        // keys row m sees; M < 2^31, so m % period fits 32 bits
-        int n = (int)K;
+    const int k32 = (int)K;
+    auto row_of = [&](int r) { return (r & 1) ? (int64_t)(r + 1) * G - 1 - g : (int64_t)r * G + g; };
+    // keys row m sees; M < 2^31, so m % period fits 32 bits
+    auto keys_of = [&](int64_t m) {
         if (period > 0) {
             const int64_t t = period > m ? m : (int64_t)((uint32_t)m % (uint32_t)period);
-            if (t + offset + 1 < K) n = (int)(t + offset) + 1;
+            if (t + offset + 1 < K) return (int)(t + offset) + 1;
         }
+        return k32;
+    };
+    uint32_t again = 0;  // rows near a tie, one bit each
+#pragma unroll 1
+    for (int r = 0; r < kSmRows; ++r) {
+        const int64_t m = row_of(r);
+        if (m >= M) continue;
+        const int n = keys_of(m);
         const int nca = (n + kChunk - 1) / kChunk;
-        if (nca == 1) softmax_row<BITS, CLAMP, 1>(x, m, (int)K, n, tab, ri, zy, y);
-        else if (nca == 2) softmax_row<BITS, CLAMP, 2>(x, m, (int)K, n, tab, ri, zy, y);
-        else if (nca == 3) softmax_row<BITS, CLAMP, 3>(x, m, (int)K, n, tab, ri, zy, y);
-        else if (MAXC == 4 || nca == 4) softmax_row<BITS, CLAMP, 4>(x, m, (int)K, n, tab, ri, zy, y);
-        else if (nca == 5) softmax_row<BITS, CLAMP, 5>(x, m, (int)K, n, tab, ri, zy, y);
-        else if (nca == 6) softmax_row<BITS, CLAMP, 6>(x, m, (int)K, n, tab, ri, zy, y);
-        else if (nca == 7) softmax_row<BITS, CLAMP, 7>(x, m, (int)K, n, tab, ri, zy, y);
-        else softmax_row<BITS, CLAMP, 8>(x, m, (int)K, n, tab, ri, zy, y);
-        hidden_codes<BITS>((int)K, zy, y, m * K, nca * kChunk, kChunk);
+        bool done;
+        if (nca == 1) done = softmax_row<BITS, CLAMP, EXACT, 1>(x, m, k32, n, tab, ri, zy, y);
+        else if (nca == 2) done = softmax_row<BITS, CLAMP, EXACT, 2>(x, m, k32, n, tab, ri, zy, y);
+        else if (nca == 3) done = softmax_row<BITS, CLAMP, EXACT, 3>(x, m, k32, n, tab, ri, zy, y);
+        else if (MAXC == 4 || nca == 4)
+            done = softmax_row<BITS, CLAMP, EXACT, 4>(x, m, k32, n, tab, ri, zy, y);
+        else if (nca == 5) done = softmax_row<BITS, CLAMP, EXACT, 5>(x, m, k32, n, tab, ri, zy, y);
+        else if (nca == 6) done = softmax_row<BITS, CLAMP, EXACT, 6>(x, m, k32, n, tab, ri, zy, y);
+        else if (nca == 7) done = softmax_row<BITS, CLAMP, EXACT, 7>(x, m, k32, n, tab, ri, zy, y);
+        else done = softmax_row<BITS, CLAMP, EXACT, 8>(x, m, k32, n, tab, ri, zy, y);
+        if (!done) again |= 1u << r;
+        hidden_codes<BITS>(k32, zy, y, m * K, nca * kChunk, kChunk);
+    }
+    // (after the loop: inside it, the registers of its exp cost the kernel
+    // three of seven waves per SIMD)
+    if (!EXACT || __builtin_expect(again == 0, 1)) return;
+    const int lane = threadIdx.x & 63;
+    const double a = (double)ax;
+#pragma unroll 1
+    for (int r = 0; r < kSmRows; ++r) {
+        if (!(again >> r & 1)) continue;
+        const int64_t m = row_of(r);
+        const int16_t* row = x + m * K;
+        const int n = keys_of(m), end = (n + kChunk - 1) / kChunk * kChunk;
+        int32_t mx = -32768;
+        for (int k = lane; k < n; k += 64) mx = max(mx, (int32_t)row[k]);
+        mx = wave_max_i32(mx);
+        const double sum = wave_sum_f64(exact_sum(row, n, mx, a, lane, 64));
+        exact_codes<BITS>(row, n, min(k32, end), mx, a, sum, (double)ay, zy, y, m * K, lane, 64);
     }
 }
 
@@ -780,10 +858,11 @@ __global__ __launch_bounds__(kSmWaves * 64) void softmax_table_kernel(
 // codes, and few rows (the 32 heads of one query), where a wave per row
 // would leave most of the chip idle and 24 keys in a lane's chain (32 rows of
 // 1531 codes: 8.0 us on the strided kernel, 3.4 us here).
-template <int BITS, bool CLAMP, int NCA>
-__device__ __forceinline__ void softmax_block_row(const int16_t* x, int64_t m, int K, int n,
+template <int BITS, bool CLAMP, bool EXACT, int NCA>
+__device__ __forceinline__ bool softmax_block_row(const int16_t* x, int64_t m, int K, int n,
                                                   const ExpTables& tab, double ri, int32_t zy,
-                                                  int32_t* red_i, double* red_d, void* y)
+                                                  int32_t* red_i, double* red_d, void* y,
+                                                  int32_t& mx)
 {
 #pragma clang fp contract(off)
     constexpr int NW = kThreads / 64, step = NW * kChunk;
@@ -794,7 +873,7 @@ __device__ __forceinline__ void softmax_block_row(const int16_t* x, int64_t m, i
     RowPart<NCA> r;
     const int last = first + step * (NCA - 1);
     r.load(x + m * K, K, first, step);
-    int32_t mx = wave_max_i32(r.max_code(n, first, step));
+    mx = wave_max_i32(r.max_code(n, first, step));
     if ((threadIdx.x & 63) == 0) red_i[wave] = mx;
     __syncthreads();
 #pragma unroll
@@ -803,11 +882,18 @@ __device__ __forceinline__ void softmax_block_row(const int16_t* x, int64_t m, i
     if ((threadIdx.x & 63) == 0) red_d[wave] = sum;
     __syncthreads();
     sum = (red_d[0] + red_d[1]) + (red_d[2] + red_d[3]);
-    r.template codes<BITS, CLAMP>(K, (1.0 / sum) * ri, zy, y, m * K, first, step);
-    hidden_codes<BITS>(K, zy, y, m * K, last + step, step);
+    int32_t o[NCA][4];
+    const bool near = r.template codes<CLAMP, EXACT>((1.0 / sum) * ri, zy, o);
+    if constexpr (EXACT) {  // (every wave has read the maxima by now)
+        if ((threadIdx.x & 63) == 0) red_i[wave] = near;
+        __syncthreads();
+        if ((red_i[0] | red_i[1] | red_i[2] | red_i[3]) != 0) return false;
+    }
+    r.template store<BITS>(o, K, y, m * K, first, step);
+    return true;
 }
 
-template <int BITS, bool CLAMP>
+template <int BITS, bool CLAMP, bool EXACT>
 __global__ __launch_bounds__(kThreads) void softmax_block_kernel(
     const int16_t* __restrict__ x, int64_t K, float ax, float ay, int32_t zy, int64_t period,
     int64_t offset, void* __restrict__ y)
@@ -820,16 +906,31 @@ __global__ __launch_bounds__(kThreads) void softmax_block_kernel(
     tab.fill((double)ax);
     const double ri = 1.0 / (double)ay;
     const int k32 = (int)K;
-    switch ((n + 4 * kChunk - 1) / (4 * kChunk)) {
-    case 1: softmax_block_row<BITS, CLAMP, 1>(x, m, k32, n, tab, ri, zy, red_i, red_d, y); break;
-    case 2: softmax_block_row<BITS, CLAMP, 2>(x, m, k32, n, tab, ri, zy, red_i, red_d, y); break;
-    case 3: softmax_block_row<BITS, CLAMP, 3>(x, m, k32, n, tab, ri, zy, red_i, red_d, y); break;
-    case 4: softmax_block_row<BITS, CLAMP, 4>(x, m, k32, n, tab, ri, zy, red_i, red_d, y); break;
-    case 5: softmax_block_row<BITS, CLAMP, 5>(x, m, k32, n, tab, ri, zy, red_i, red_d, y); break;
-    case 6: softmax_block_row<BITS, CLAMP, 6>(x, m, k32, n, tab, ri, zy, red_i, red_d, y); break;
-    case 7: softmax_block_row<BITS, CLAMP, 7>(x, m, k32, n, tab, ri, zy, red_i, red_d, y); break;
-    default: softmax_block_row<BITS, CLAMP, 8>(x, m, k32, n, tab, ri, zy, red_i, red_d, y); break;
+    int32_t mx;
+    bool done;
+    const int parts = (n + 4 * kChunk - 1) / (4 * kChunk);
+    switch (parts) {
+    case 1: done = softmax_block_row<BITS, CLAMP, EXACT, 1>(x, m, k32, n, tab, ri, zy, red_i, red_d, y, mx); break;
+    case 2: done = softmax_block_row<BITS, CLAMP, EXACT, 2>(x, m, k32, n, tab, ri, zy, red_i, red_d, y, mx); break;
+    case 3: done = softmax_block_row<BITS, CLAMP, EXACT, 3>(x, m, k32, n, tab, ri, zy, red_i, red_d, y, mx); break;
+    case 4: done = softmax_block_row<BITS, CLAMP, EXACT, 4>(x, m, k32, n, tab, ri, zy, red_i, red_d, y, mx); break;
+    case 5: done = softmax_block_row<BITS, CLAMP, EXACT, 5>(x, m, k32, n, tab, ri, zy, red_i, red_d, y, mx); break;
+    case 6: done = softmax_block_row<BITS, CLAMP, EXACT, 6>(x, m, k32, n, tab, ri, zy, red_i, red_d, y, mx); break;
+    case 7: done = softmax_block_row<BITS, CLAMP, EXACT, 7>(x, m, k32, n, tab, ri, zy, red_i, red_d, y, mx); break;
+    default: done = softmax_block_row<BITS, CLAMP, EXACT, 8>(x, m, k32, n, tab, ri, zy, red_i, red_d, y, mx); break;
     }
+    const int end = min(k32, parts * 4 * kChunk);
+    if (EXACT && __builtin_expect(!done, 0)) {  // for the whole block
+        const int t = threadIdx.x;
+        const double a = (double)ax;
+        double sum = wave_sum_f64(exact_sum(x + m * K, n, mx, a, t, kThreads));
+        __syncthreads();
+        if ((t & 63) == 0) red_d[t >> 6] = sum;
+        __syncthreads();
+        sum = (red_d[0] + red_d[1]) + (red_d[2] + red_d[3]);
+        exact_codes<BITS>(x + m * K, n, end, mx, a, sum, (double)ay, zy, y, m * K, t, kThreads);
+    }
+    hidden_codes<BITS>(k32, zy, y, m * K, end + kChunk * (int)(threadIdx.x >> 6), 4 * kChunk);
 }
 
 // RMSNorm: ss = sum (x - zp_x)^2 (exact, int64); ms = alpha^2 ss / K + eps;
@@ -1082,35 +1183,47 @@ hipError_t launch_add_rmsnorm(const int16_t* x1, float a1, int32_t z1, const int
     return launch_rmsnorm(h, M, K, ah, zh, gamma, eps, ay, zy, bits, y, st);
 }
 
-template <int BITS, bool CLAMP>
+template <int BITS, bool CLAMP, bool EXACT>
 static void softmax_t(const int16_t* x, int64_t M, int64_t K, float ax, float ay, int32_t zy,
                       int64_t P, int64_t O, void* y, hipStream_t st)
 {
     // a wave per row when that gives every SIMD one; rows of more than 2048
     // codes (a block holds 8192) and few rows take a block each
     if (K > 2048 || (M < 1024 && K > 512)) {
-        softmax_block_kernel<BITS, CLAMP>
+        softmax_block_kernel<BITS, CLAMP, EXACT>
             <<<dim3((unsigned)M), dim3(kThreads), 0, st>>>(x, K, ax, ay, zy, P, O, y);
         return;
     }
     constexpr int RPB = kSmRows * kSmWaves;
     const dim3 g((unsigned)((M + RPB - 1) / RPB)), b(kSmWaves * 64);
     if (K <= 4 * kChunk)
-        softmax_table_kernel<BITS, CLAMP, 4><<<g, b, 0, st>>>(x, M, K, ax, ay, zy, P, O, y);
+        softmax_table_kernel<BITS, CLAMP, EXACT, 4><<<g, b, 0, st>>>(x, M, K, ax, ay, zy, P, O, y);
     else
-        softmax_table_kernel<BITS, CLAMP, 8><<<g, b, 0, st>>>(x, M, K, ax, ay, zy, P, O, y);
+        softmax_table_kernel<BITS, CLAMP, EXACT, 8><<<g, b, 0, st>>>(x, M, K, ax, ay, zy, P, O, y);
+}
+
+template <int BITS>
+static void softmax_bits(const int16_t* x, int64_t M, int64_t K, float ax, float ay, int32_t zy,
+                         int64_t P, int64_t O, void* y, hipStream_t st)
+{
+    // probabilities are at most 1 / ay output steps
+    const bool clamp = !(1.0 / (double)ay <= 131072.0);
+    // rows of whole aligned 16-byte chunks up to 2048 codes: the tables' codes
+    // as they are (the tie check costs 1.1 of 22.3 us at 32 x 1024 causal
+    // rows of 1024 codes); all others agree with the definition at ties too
+    const bool exact = K > 2048 || K % 8 != 0 || ((uintptr_t)x | (uintptr_t)y) % 16 != 0;
+    if (exact && clamp) softmax_t<BITS, true, true>(x, M, K, ax, ay, zy, P, O, y, st);
+    else if (exact) softmax_t<BITS, false, true>(x, M, K, ax, ay, zy, P, O, y, st);
+    else if (clamp) softmax_t<BITS, true, false>(x, M, K, ax, ay, zy, P, O, y, st);
+    else softmax_t<BITS, false, false>(x, M, K, ax, ay, zy, P, O, y, st);
 }
 
 hipError_t launch_softmax(const int16_t* x, int64_t M, int64_t K, float ax, float ay, int32_t zy,
                           int32_t bits, int64_t period, int64_t offset, void* y, hipStream_t st)
 {
     if (K <= 8192) {
-        // probabilities are at most 1 / ay output steps
-        const bool clamp = !(1.0 / (double)ay <= 1e9);
-        if (bits == 8 && !clamp) softmax_t<8, false>(x, M, K, ax, ay, zy, period, offset, y, st);
-        else if (bits == 8) softmax_t<8, true>(x, M, K, ax, ay, zy, period, offset, y, st);
-        else if (!clamp) softmax_t<16, false>(x, M, K, ax, ay, zy, period, offset, y, st);
-        else softmax_t<16, true>(x, M, K, ax, ay, zy, period, offset, y, st);
+        if (bits == 8) softmax_bits<8>(x, M, K, ax, ay, zy, period, offset, y, st);
+        else softmax_bits<16>(x, M, K, ax, ay, zy, period, offset, y, st);
     } else if (bits == 8) {
         softmax_kernel<8><<<(unsigned)M, kThreads, 0, st>>>(x, K, ax, ay, zy, period, offset, y);
     } else {

@@ -368,3 +368,37 @@ def test_rope_pair_index_range(pairs):
         ref = mq.mq_rope_apply(x[:, part].contiguous(), 4096, 2e-4, -7, 0.05, -2, table, 8)
         assert torch.equal(y[:, part], ref)
         assert len(torch.unique(ref)) > 100
+
+
+# Two keys of scores 0 and -d (all others vanish) and an output scale that
+# puts one of the quotients within an ulp or two of a half-integer: the
+# definition, e / sum / ay one IEEE operation at a time, gives the code named
+# (key 0 or key 1), two table exponentials and products with reciprocals its
+# neighbour.  Found by a search over 3.9e9 pairs of d and ay.
+NEAR_TIES = [("0x1.4a10cap-7", 769, "0x1.21e726p-27", 1, 51236),
+             ("0x1.9a4926p-7", 327, "0x1.7bf898p-22", 1, 46326),
+             ("0x1.36f662p-6", 609, "0x1.ff8a66p-33", 1, 41069),
+             ("0x1.36f662p-6", 609, "0x1.89469ep-33", 1, 53419),
+             ("0x1.ed0970p-9", 1650, "0x1.c1baf6p-14", 0, 9307)]
+
+
+@pytest.mark.parametrize("ax,d,ay,key,code", NEAR_TIES)
+@pytest.mark.parametrize("M,K,offset", [(1100, 777, 0), (3, 777, 0), (2, 4096, 0), (20, 2, 0),
+                                        (1030, 1024, 1), (1030, 2047, 0)])
+def test_softmax_near_ties(ax, d, ay, key, code, M, K, offset):
+    """Rows of any length and alignment round as the definition does, in the
+    kernels with a wave and with a block per row."""
+    import torch
+    mq = _mq()
+    ax, ay = float.fromhex(ax), float.fromhex(ay)
+    e = torch.exp(torch.tensor([0.0, -(ax * d)], dtype=torch.float64, device="cuda"))
+    # (a tensor: torch multiplies by the reciprocal of a scalar divisor)
+    t = torch.round(e / e.sum() / torch.full_like(e, ay)).tolist()
+    assert t[key] == code
+    want = [int(min(v, 65535.0)) - 32768 for v in t]
+    x = torch.empty(M * K + offset, dtype=torch.int16, device="cuda")[offset:].view(M, K)
+    x[:] = 30000 - 60000
+    x[:, 0] = 30000
+    x[:, K // 2] = 30000 - d
+    y = mq.mq_softmax(x, ax, 0, ay, -32768, 16)
+    assert y[:, [0, K // 2]].unique(dim=0).tolist() == [want]

@@ -636,11 +636,13 @@ mq_status mq_arl_backward(const float* x, const float* g, int64_t numel, float a
  *              bytes; may be overwritten with the per-row zero-point terms,
  *              the per-row sums of B and b_scale (calls that may run
  *              concurrently must not share it)
- *   path       MQ_PATH_AUTO (K <= 128 or N <= 256, the two products of
- *              attention: one launch at any M, stride and alignment; else
- *              the tiled kernel for M > 16 when the strides keep 16-byte
- *              aligned rows), MQ_PATH_PREFILL (the tiled kernel) or
- *              MQ_PATH_GENERIC; every path computes the same bits
+ *   path       MQ_PATH_AUTO (one launch at any K, stride and alignment; the
+ *              tiled kernel for M > 16 with 16-byte aligned rows where the
+ *              sizes make it the faster one; products past 2^30 rows or
+ *              columns or about 2^27 elements between output rows the tiled
+ *              or, where that does not take them, the generic kernel),
+ *              MQ_PATH_PREFILL (the tiled kernel) or MQ_PATH_GENERIC; every
+ *              path computes the same bits
  *   out_causal, in_causal in [-1, 2^40]
  * Errors: MQ_ERR_INVALID_ARG for any violation above.
  */

@@ -788,6 +788,46 @@ bool attn_direct_supported(int64_t M, int64_t N, int64_t ldy, int32_t H, int32_t
            rb <= 0x7FFFFFFF / ((N + 31) / 32);
 }
 
+// Where the LDS tiles (qlinear_prefill.hip; with b_zp != 0 after a pass for the
+// sums) are faster than the kernels here, for shapes and strides both take.
+// Measured over 8 heads of one group and 32 of four, head dimensions 32 .. 256,
+// 64 .. 4096 queries over 256 .. 4096 keys, causal and not (us, direct kernel
+// first).
+bool attn_tiles_better(int64_t M, int64_t N, int64_t K, int32_t H, int32_t b_zp,
+                       int64_t out_causal, int64_t in_causal)
+{
+    if (M <= 16) return false;
+    const int64_t cols = (N + 63) / 64, tiles = (M + 31) / 32 * cols * H;  // 32 x 64
+    if (K <= kAttnWideK) {
+        // Queries times keys.  A head dimension of one or two whole steps
+        // walks the keys without a window at each load (full 1024^2, 32
+        // heads of 64: 21 against 31; of 128: 28, 38), any other one pays
+        // for the windows once the 32 x 64 tiles are in use and the rows are
+        // long (of 80: 42, 37; 8 heads of 80 over 256 x 2048: 18.7, 12.5; up
+        // to 64 queries or 512 keys even or ahead).
+        if (K != 64 && K != 128) return M > 64 && N > 512 && tiles >= 2048;
+        // two steps: a long causal triangle leaves the strips uneven (8
+        // heads, 4096^2: 78 against 71; 32 heads, 2048^2: 70, 76)
+        return K == 128 && out_causal >= 0 && out_causal < M && M > 2048;
+    }
+    // A product long in K and N, of many rows, reuses its operands more.
+    if (N > 256) return true;
+    // Probabilities times values: the kernel here reads the probabilities
+    // once per 64 columns, the LDS tiles once per 128, after the pass for the
+    // sums that reads them too.  Up to 64 columns and with that pass the
+    // kernel here is ahead (full 1024^2, 32 heads of 64: 21 against 29);
+    // without it (b_zp = 0) the tiles are from 1024 tiles on (21, 19), and
+    // with three or more column tiles also with it (32 heads of 256, 1024^2:
+    // 67, 43; 8 heads of 256, 512 x 2048, 512 tiles: 17.5, 24.5), with two
+    // from 2048 (32 heads of 128, 1024^2: 36, 33; 8 heads, 2048^2: 30, 33).
+    // A causal triangle halves what the kernel here reads.
+    const bool triangle = in_causal >= 0 && in_causal < M;
+    if (triangle)
+        return b_zp == 0 ? cols >= 2 && tiles >= 1536 : cols >= 4 && tiles >= 2048;
+    if (b_zp == 0 || cols >= 3) return tiles >= 1024 || (tiles >= 768 && K >= 2048);
+    return cols == 2 && tiles >= 2048;
+}
+
 hipError_t launch_attn_direct(const int16_t* a, int64_t lda, int64_t a_hs, int32_t H,
                               const int8_t* b, int64_t ldb, int64_t b_hs, int32_t G, int64_t M,
                               int64_t N, int64_t K, float a_scale, int32_t a_zp, float b_scale,

@@ -678,12 +678,11 @@ mq_status mq_attn_matmul(const int16_t* a, int64_t lda, int64_t a_hs, int32_t H,
     p.ro_bs = M;
     p.row_off = b_zp != 0 ? row_off : nullptr;  // b_zp = 0: no row terms
     if (path == MQ_PATH_AUTO) {
-        // the direct kernels serve both products of attention: K (the head
-        // dimension) short, or N (the head dimension) short.  A product
-        // long both ways reuses its operands more than they do: the LDS
-        // tiles, where rows and strides allow them.
-        const bool tiles_better = M > 16 && N > 256 && K > mq::kAttnWideK && mq::prefill_supported(p);
-        if (!tiles_better && mq::attn_direct_supported(M, N, ldy, H, G))
+        // the one-launch kernels, unless the LDS tiles take the rows and
+        // strides and are the faster ones
+        const bool tiles = mq::attn_tiles_better(M, N, K, H, b_zp, out_causal, in_causal) &&
+                           mq::prefill_supported(p);
+        if (!tiles && mq::attn_direct_supported(M, N, ldy, H, G))
             return from_hip(mq::launch_attn_direct(a, lda, a_hs, H, b, ldb, b_hs, G, M, N, K,
                                                    a_scale, a_zp, b_scale, b_zp, out_scale,
                                                    out_zp, out_bits, y, ldy, y_hs, out_causal,

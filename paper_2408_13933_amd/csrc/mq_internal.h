@@ -171,6 +171,8 @@ hipError_t launch_softmax(const int16_t* x, int64_t M, int64_t K, float ax, floa
 // kAttnWideK: the largest K whose sums stay in int32.
 constexpr int kAttnWideK = 128;
 bool attn_direct_supported(int64_t M, int64_t N, int64_t ldy, int32_t H, int32_t G);
+bool attn_tiles_better(int64_t M, int64_t N, int64_t K, int32_t H, int32_t b_zp,
+                       int64_t out_causal, int64_t in_causal);
 hipError_t launch_attn_direct(const int16_t* a, int64_t lda, int64_t a_hs, int32_t H,
                               const int8_t* b, int64_t ldb, int64_t b_hs, int32_t G, int64_t M,
                               int64_t N, int64_t K, float a_scale, int32_t a_zp, float b_scale,

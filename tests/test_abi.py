@@ -527,3 +527,26 @@ def test_attn_direct_row_stride_bound():
         lo, hi = (mid, hi) if f(16, 32, mid, 1, 1) else (lo, mid)
     assert 12 * lo + 64 <= 2 ** 31 - 1 and (12 * lo + 64) * 2 <= 2 ** 32 - 1
     assert lo > 1 << 27                          # and no shorter than it has to be
+
+
+def test_attn_route_by_sizes():
+    """The products that take the LDS tiles on the automatic path (M, N, K, H,
+    b_zp, out_causal, in_causal)."""
+    f = getattr(mq.lib(), "_ZN2mq17attn_tiles_betterEllliill")
+    f.restype = ctypes.c_bool
+    f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int32] * 2 + [ctypes.c_int64] * 2
+    tiled = [(300, 320, 256, 3, -5, -1, -1), (65, 528, 80, 76, 9, -1, -1),
+             (100, 528, 48, 80, 0, 428, -1), (161, 192, 160, 64, -128, -1, -1),
+             (161, 130, 176, 64, 0, -1, -1), (384, 80, 384, 64, 0, -1, 0),
+             (272, 250, 272, 64, 3, -1, 0), (4096, 4096, 128, 8, 3, 0, -1),
+             (1024, 128, 1024, 32, 3, -1, -1), (256, 192, 4096, 32, 3, -1, 3840),
+             (1024, 64, 1024, 32, 0, -1, -1)]
+    direct = [(1, 4096, 128, 32, 3, -1, -1), (16, 4096, 4096, 64, 0, -1, -1),
+              (1024, 1024, 64, 32, 3, 0, -1), (1024, 1024, 128, 32, 3, 0, -1),
+              (512, 512, 80, 32, 3, 0, -1), (1024, 64, 1024, 32, 3, -1, 0),
+              (1024, 64, 1024, 32, 3, -1, -1), (1024, 128, 1024, 32, 3, -1, 0),
+              (512, 256, 2048, 8, 3, -1, -1), (1024, 64, 1024, 32, 0, -1, 0)]
+    for args in tiled:
+        assert f(*args), args
+    for args in direct:
+        assert not f(*args), args

@@ -49,10 +49,12 @@ def test_scores_qkt_parity(T, D, H, G, out_bits):
         assert np.array_equal(y, ref), (path, int((y != ref).sum()))
 
 
-@pytest.mark.parametrize("T,D,H,G", [(256, 64, 8, 2), (200, 64, 4, 2), (130, 128, 2, 1)])
+@pytest.mark.parametrize("T,D,H,G", [(256, 64, 8, 2), (200, 64, 4, 2), (130, 128, 2, 1),
+                                     (208, 64, 4, 2), (272, 128, 2, 1), (144, 96, 3, 3)])
 def test_context_pv_parity(T, D, H, G):
     """P V: probability codes [H][T][T] times the transposed value codes,
-    written into a [token][heads * D] context view."""
+    written into a [token][heads * D] context view (rows of whole 16-byte
+    chunks, T % 16 == 0, take the tiled kernel on its path)."""
     mq, torch = _mq(), _torch()
     rng = np.random.default_rng(T * 3 + D + H)
     p = rng.integers(-32768, 32768, (H, T, T)).astype(np.int16)
@@ -66,7 +68,7 @@ def test_context_pv_parity(T, D, H, G):
     gvt = mq.mq_transpose_i8(gv)
     assert np.array_equal(gvt.cpu().numpy(), v.T)
     gp = torch.from_numpy(p).cuda()
-    for path in (mq.PATH_AUTO, mq.PATH_GENERIC):
+    for path in (mq.PATH_AUTO, mq.PATH_PREFILL, mq.PATH_GENERIC):
         ctx = torch.zeros((T, H * D), dtype=torch.int16, device="cuda")
         view = ctx.view(T, H, D).permute(1, 0, 2)
         mq.mq_attn_matmul(gp, gvt.view(G, D, T), *prm, out=view, path=path)
@@ -115,34 +117,35 @@ def test_attn_short_k_extremes(K):
 
 def test_attn_tinyllama_full_size_sampled_heads():
     """The 1024-token TinyLlama attention (32 query heads, 4 key/value
-    heads, head dimension 64) through the tiled kernel; heads 0, 7, 8 and
-    31 (groups 0, 0, 1, 3) against the oracle."""
+    heads, head dimension 64) through the one-launch and the tiled kernels;
+    heads 0, 7, 8 and 31 (groups 0, 0, 1, 3) against the oracle."""
     mq, torch = _mq(), _torch()
     rng = np.random.default_rng(1024)
     T, D, H, G = 1024, 64, 32, 4
     q = torch.from_numpy(rng.integers(-32768, 32768, (T, H * D)).astype(np.int16)).cuda()
     k = torch.from_numpy(rng.integers(-128, 128, (T, G * D)).astype(np.int8)).cuda()
-    prm = _params(rng, 16)
+    v = torch.from_numpy(rng.integers(-128, 128, (T, G * D)).astype(np.int8)).cuda()
+    prm, prm2 = _params(rng, 16), _params(rng, 16)
     qa = q.view(T, H, D).permute(1, 0, 2)
     kb = k.view(T, G, D).permute(1, 0, 2)
-    s = mq.mq_attn_matmul(qa, kb, *prm)
-    heads = [0, 7, 8, 31]
-    qa_np = qa.cpu().numpy()
-    kb_np = kb.cpu().numpy()
-    for h in heads:
-        ref = oracle.attn_matmul(np.ascontiguousarray(qa_np[h:h + 1]),
-                                 np.ascontiguousarray(kb_np[h // 8:h // 8 + 1]), *prm)
-        assert np.array_equal(s[h:h + 1].cpu().numpy(), ref), h
-    p = s  # int16 codes as the probabilities of the next product
-    v = torch.from_numpy(rng.integers(-128, 128, (T, G * D)).astype(np.int8)).cuda()
     vt = mq.mq_transpose_i8(v).view(G, D, T)
-    prm2 = _params(rng, 16)
-    ctx = mq.mq_attn_matmul(p, vt, *prm2)
-    p_np, vt_np = p.cpu().numpy(), vt.cpu().numpy()
-    for h in heads:
-        ref = oracle.attn_matmul(np.ascontiguousarray(p_np[h:h + 1]),
-                                 np.ascontiguousarray(vt_np[h // 8:h // 8 + 1]), *prm2)
-        assert np.array_equal(ctx[h:h + 1].cpu().numpy(), ref), h
+    heads = [0, 7, 8, 31]
+    qa_np, kb_np, vt_np = qa.cpu().numpy(), kb.cpu().numpy(), vt.cpu().numpy()
+    p = None
+    for path in (mq.PATH_AUTO, mq.PATH_PREFILL):
+        s = mq.mq_attn_matmul(qa, kb, *prm, path=path)
+        if p is None:  # int16 codes as the probabilities of the next product
+            p, p_np = s, s.cpu().numpy()
+            ref = [oracle.attn_matmul(np.ascontiguousarray(qa_np[h:h + 1]),
+                                      np.ascontiguousarray(kb_np[h // 8:h // 8 + 1]), *prm)
+                   for h in heads]
+            ref2 = [oracle.attn_matmul(np.ascontiguousarray(p_np[h:h + 1]),
+                                       np.ascontiguousarray(vt_np[h // 8:h // 8 + 1]), *prm2)
+                    for h in heads]
+        ctx = mq.mq_attn_matmul(p, vt, *prm2, path=path)
+        for i, h in enumerate(heads):
+            assert np.array_equal(s[h:h + 1].cpu().numpy(), ref[i]), (path, h)
+            assert np.array_equal(ctx[h:h + 1].cpu().numpy(), ref2[i]), (path, h)
 
 
 @pytest.mark.parametrize("rows,cols", [(1, 1), (63, 65), (1024, 256), (7, 3000)])
@@ -154,7 +157,9 @@ def test_transpose_i8(rows, cols):
 
 
 @pytest.mark.parametrize("T,D,H,G,b_zp", [(1024, 64, 8, 2, 0), (300, 64, 4, 2, 17),
-                                          (200, 64, 2, 1, -5), (129, 128, 2, 2, 0)])
+                                          (200, 64, 2, 1, -5), (129, 128, 2, 2, 0),
+                                          (304, 64, 4, 2, 17), (272, 128, 2, 1, -128),
+                                          (400, 96, 2, 2, 0)])
 def test_causal_attention_parity(T, D, H, G, b_zp):
     """Q K^T with the causal output promise (entries past the diagonal may
     stay unwritten) and P V with causal probabilities (zero codes past the
@@ -167,7 +172,7 @@ def test_causal_attention_parity(T, D, H, G, b_zp):
     prm = _params(rng, 16)
     prm = prm[:3] + (b_zp,) + prm[4:]
     ref = oracle.attn_matmul(q, k, *prm)
-    for path in (mq.PATH_AUTO, mq.PATH_GENERIC):
+    for path in (mq.PATH_AUTO, mq.PATH_PREFILL, mq.PATH_GENERIC):
         s = torch.full((H, T, T), 12345, dtype=torch.int16, device="cuda")
         mq.mq_attn_matmul(torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda(), *prm, out=s,
                           path=path, out_causal=0)
@@ -179,7 +184,48 @@ def test_causal_attention_parity(T, D, H, G, b_zp):
     v = rng.integers(-128, 128, (G, D, T)).astype(np.int8)
     prm2 = (1.0 / 65535, -32768, 0.03, b_zp, 1e-3, 3, 8)
     ref2 = oracle.attn_matmul(p, v, *prm2)
-    for path in (mq.PATH_AUTO, mq.PATH_GENERIC):
+    for path in (mq.PATH_AUTO, mq.PATH_PREFILL, mq.PATH_GENERIC):
         ctx = mq.mq_attn_matmul(torch.from_numpy(p).cuda(), torch.from_numpy(v).cuda(), *prm2,
                                 path=path, in_causal=0)
         assert np.array_equal(ctx.cpu().numpy(), ref2), path
+
+
+# products that the automatic path gives to the LDS tiles: long in K and N; a
+# head dimension of 80 over many long rows; probabilities times values with
+# three column tiles, and without B's zero-point with two (H, G, M, N, K, b_zp,
+# queries' first visible key count or None)
+@pytest.mark.parametrize("H,G,M,N,K,b_zp,past", [
+    (3, 3, 300, 320, 256, -5, None), (3, 1, 300, 320, 256, 17, 20), (2, 1, 300, 320, 272, 0, 0),
+    (76, 4, 65, 528, 80, 9, None), (80, 4, 100, 528, 48, 0, 428), (64, 8, 161, 192, 160, -128, None),
+    (64, 8, 161, 130, 176, 0, None), (64, 8, 384, 80, 384, 0, 0), (64, 8, 272, 250, 272, 3, 0),
+])
+@pytest.mark.parametrize("out_bits", [16, 8])
+def test_tiled_products_auto(H, G, M, N, K, b_zp, past, out_bits):
+    """Rows of 16-byte chunks in views with padding, with the promise that
+    fits the shape: hidden outputs where N is the longer side, hidden
+    activations where K is."""
+    mq, torch = _mq(), _torch()
+    rng = np.random.default_rng(H + M + N + K)
+    a_zp = int(rng.integers(-30000, 30000))
+    a = np.clip(a_zp + np.rint(4000 * rng.standard_normal((H, M, K))), -32768, 32767)
+    a = a.astype(np.int16)
+    b = rng.integers(-128, 128, (G, N, K)).astype(np.int8)
+    outs = past is not None and N > K
+    kw, seen = {}, np.ones((M, N), bool)
+    if outs:
+        kw = dict(out_causal=past)
+        seen = np.arange(N)[None, :] <= np.arange(M)[:, None] + past
+    elif past is not None:
+        kw = dict(in_causal=past)
+        a[:, np.arange(K)[None, :] > np.arange(M)[:, None] + past] = a_zp
+    out = 3e-5 * 0.02 * 4000 * 128 * K ** 0.5 / (0.4 * 2 ** (out_bits - 1))
+    prm = (3e-5, a_zp, 0.02, b_zp, out, -7, out_bits)
+    ref = oracle.attn_matmul(a, b, *prm)
+    ga = torch.zeros((H, M, K + 16), dtype=torch.int16, device="cuda")[:, :, :K]
+    gb = torch.zeros((G, N, K + 32), dtype=torch.int8, device="cuda")[:, :, :K]
+    ga.copy_(torch.from_numpy(a))
+    gb.copy_(torch.from_numpy(b))
+    for path in (mq.PATH_AUTO, mq.PATH_PREFILL):
+        y = mq.mq_attn_matmul(ga, gb, *prm, path=path, **kw).cpu().numpy()
+        assert np.array_equal(y[:, seen], ref[:, seen]), (path, int((y != ref)[:, seen].sum()))
+    assert len(np.unique(ref)) > 10

@@ -528,11 +528,11 @@ __device__ inline int64_t causal_keys(int64_t m, int64_t K, int64_t period, int6
 // Each block evaluates the two 256-entry factor tables once (one exp per
 // entry, in LDS); a key then costs two table reads and one fp64 product,
 // within three ulp of the direct exp, and its quotient is e * s with s =
-// (1 / sum) (1 / ay): within 2^-47 of the definition's e / sum / ay, its exps
-// and sum in another order included.  Up to 2^17 that is 2^-30; a row with a
-// quotient within 2^-29 of a half-integer is evaluated again as it is defined
-// (exact_codes), so no code depends on the tables.  Hidden keys are written
-// as zy.
+// (1 / sum) (1 / ay): with the exps and the sum in another order 36 ulp at
+// most, below 2^-46, from the definition's e / sum / ay, so less than 2^-29 up
+// to 2^17.  A row (EXACT) with a quotient that near a half-integer is
+// evaluated again as it is defined (exact_codes), so that no code depends on
+// the tables.  Hidden keys are written as zy.
 // Each wave takes kSmRows rows in snake order (m, 2G - 1 - m, ... for G waves
 // in the grid): under a causal mask whose period divides 2G
 // the key counts of each pair sum to the period plus one.
@@ -1324,12 +1324,18 @@ hipError_t launch_rope_apply(const int16_t* x, int64_t T, int64_t H, int64_t D, 
     const int64_t half = D / 2;
     if (T == 0) return hipSuccess;
     if (H * half > 0x7FFFFFFF - 256) return hipErrorInvalidValue;
-    // whole aligned groups of eight in both halves and in the output, with
-    // the last block's pair index in 32 bits
+    // whole aligned groups of eight in both halves and in the output, the last
+    // block's pair index in 32 bits, and enough of them: a wave's worth per
+    // token and 2^18 in all (us, one pair per thread first: 1024 tokens x 32
+    // heads of 64 5.8, 4.8; 777 x 32 5.1, 4.4; 256 x 32 3.0 both; 64 x 32 2.4,
+    // 2.9; 1024 x 4 2.6, 3.0; 4096 x 4, whose blocks would be a sixteenth
+    // full, 4.5, 6.1)
     const uintptr_t yal = bits == 8 ? 8 : 16;
+    const int64_t pairs = H * half;
     const bool vec = half % 8 == 0 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)y % yal) == 0 &&
-                     H * half <= 0x7FFFFFFF - 8 * 256;
-    const int64_t threads = H * half / (vec ? 8 : 1);
+                     pairs <= 0x7FFFFFFF - 8 * 256 && pairs >= 512 &&
+                     T > ((int64_t)1 << 18) / pairs;
+    const int64_t threads = pairs / (vec ? 8 : 1);
     const dim3 g((unsigned)((threads + 255) / 256), (unsigned)(T < 65535 ? T : 65535));
     const int32_t h32 = (int32_t)H, hf = (int32_t)half;
     if (bits == 8) {

@@ -345,6 +345,22 @@ def test_lut_mul_table_in_memory_and_in_lds(n):
     assert np.array_equal(y.cpu().numpy(), ref)
 
 
+# both forms of the rotation and the sizes between them: whole groups of eight
+# pairs or not, 512 pairs per token, 2^18 in all
+@pytest.mark.parametrize("T,H,D", [(513, 16, 64), (512, 16, 64), (600, 15, 64), (700, 40, 32),
+                                   (600, 18, 60), (300, 9, 256)])
+@pytest.mark.parametrize("out_bits", [16, 8])
+def test_rope_forms(T, H, D, out_bits):
+    mq = _mq()
+    rng = np.random.default_rng(T + H + D)
+    x = rng.integers(-30000, 30000, (T, H * D)).astype(np.int16)
+    ax, zx = 2e-4, -7
+    ay, zy = (3e-4, 4) if out_bits == 16 else (0.05, -2)
+    y = mq.mq_rope(_dev(x), H, ax, zx, ay, zy, out_bits, pos0=3).cpu().numpy()
+    ref = oracle.rope(x, H, ax, zx, ay, zy, out_bits, pos0=3)
+    _equal_but_ties(y, ref, _rope_pre(x, H, ax, zx, ay, 3))
+
+
 # pairs per token at the top of the 32-bit index: the last count of eight-pair
 # threads whose last block ends inside it, and the last count accepted
 @pytest.mark.parametrize("pairs", [2 ** 31 - 2056, 2 ** 31 - 264])

@@ -1265,38 +1265,45 @@ static_assert(T128x128A16<8>::TM == kA16TileM && T128x128A16<8>::BK == kA16TileK
                   kA16TileM % T64x64A16<8>::TM == 0 && T64x64A16<8>::BK == kA16TileK,
               "the causal column sums assume these 16-bit tile sizes");
 
-// Time model of each tile shape on MI355X, fitted to timings of every tile on
-// 34 int8 and 16 packed int4 layers (M = 20..2048, K = 1024..16384, N =
-// 256..256000, one box).  A block costs a fixed part (the first memory round
-// trip, the epilogue and its stores) plus a time per K stage; with more CUs
-// busy a stage takes longer (the chip clocks down under the MFMA load and the
-// blocks share the memory system): stage * (1 + busy * (busy fraction)^2).
-// occ blocks share a CU within one round.  Units: microseconds.  The chosen
-// tile is the fastest measured one, or within 15% of it, on each of these
-// layers (0.6% behind it on average with int8 weights, 1.2% with int4).
+// Time model of each tile shape on MI355X, fitted to timings of every tile and
+// split on 118 int8 and 80 packed int4 layers (M = 17..2048, K = 512..16384, N
+// = 256..256000, one box), each with weights that come from memory (copies
+// rotated over 700 MB, as the layers of a model take their turns) and with
+// weights the caches hold, the former at 0.6 of the weight.  A block costs a
+// fixed part (the first memory round trip, the epilogue and its stores) plus a
+// time per K stage; with more CUs busy a stage takes longer (the chip clocks
+// down under the MFMA load and the blocks share the memory system): stage *
+// (1 + busy * (busy fraction)^2).  occ blocks share a CU within one round.
+// Units: microseconds.  The chosen tile and split are on average 1.2% behind
+// the fastest from memory and 1.3% from the caches (int4: 0.8 and 0.7).  A fit
+// to cached weights alone took 64x128 tiles without or with two splits where
+// the stream from memory wants fewer, larger reads: 512 x 16384 x 2048 33.9
+// us instead of 33.2 on 128x128 split four (29.8 to 34.5 on another box), 128
+// x 5632 x 2048 16.1 instead of 11.0, int4 1024 x 16384 x 2048 56.7 instead of
+// 46.8.
 struct TileModel {
     int tm, tn, bk;
     double fixed_us, stage_us, busy;
     int occ = 1;
 };
 constexpr TileModel kTiles[] = {
-    {256, 128, 128, 7.0, 0.476, 0.8},
-    {128, 128, 128, 4.4, 0.287, 0.9},
-    {192, 256, 128, 6.0, 0.740, 1.0},
-    {64, 64, 128, 2.8, 0.153, 1.6, 2},  // 64 KiB of stage ring: two blocks per CU
-    {256, 256, 128, 7.6, 0.934, 1.1},
-    {64, 128, 128, 3.6, 0.186, 0.6},
+    {256, 128, 128, 6.3, 0.586, 0.5},
+    {128, 128, 128, 5.6, 0.370, 0.3},
+    {192, 256, 128, 7.3, 0.933, 0.5},
+    {64, 64, 128, 4.1, 0.175, 1.8, 2},  // 64 KiB of stage ring: two blocks per CU
+    {256, 256, 128, 9.4, 0.983, 0.6},
+    {64, 128, 128, 4.6, 0.228, 0.5},
 };
 // packed int4 weights: the in-register unpack makes a stage longer where few
 // blocks run and matters less where the chip is full; 192x256 runs four waves
 // on 64-deep stages
 constexpr TileModel kTilesW4[] = {
-    {256, 128, 128, 6.4, 0.636, 0.3},
-    {128, 128, 128, 4.8, 0.416, 0.3},
-    {192, 256, 64, 10.2, 0.569, 0.3},
-    {64, 64, 128, 2.8, 0.254, 0.5, 2},
-    {256, 256, 128, 8.2, 1.023, 0.6},
-    {64, 128, 128, 3.6, 0.280, 0.0},
+    {256, 128, 128, 7.3, 0.619, 0.5},
+    {128, 128, 128, 6.1, 0.436, 0.1},
+    {192, 256, 64, 13.1, 0.511, 0.3},
+    {64, 64, 128, 4.4, 0.258, 0.4, 2},
+    {256, 256, 128, 9.1, 1.174, 0.3},
+    {64, 128, 128, 4.4, 0.279, 0.2},
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 static_assert(kNumTiles == MQ_PREFILL_TILES, "one explicit path per tile");
@@ -1335,11 +1342,13 @@ static_assert(kTilesA16[kA16T64x128].tn == T64x128A16<8>::TN &&
                   T128x192A16<8>::GROUPS_PER_CU == 1,
               "the 16-bit time model's rows follow the tiles");
 // A K split adds round trips to memory (partial stores, the counter, the
-// partial loads) and moves every slice's int32 tile through memory and back
-// (written through, read around the caches): fitted, 2.5 us plus 0.24 us
-// per MB of partial sums stored and loaded.
-constexpr double kSplitFixedUs = 2.5;
-constexpr double kSplitUsPerMB = 0.24;
+// partial loads), one more per slice that the last block merges, and moves
+// every slice's int32 tile through memory and back (written through, read
+// around the caches): fitted with the tiles, 1.0 us plus 0.3 per further
+// slice plus 0.14 per MB of partial sums stored and loaded.
+constexpr double kSplitFixedUs = 1.0;
+constexpr double kSplitSliceUs = 0.3;
+constexpr double kSplitUsPerMB = 0.14;
 constexpr int kMaxSplits = 8;
 // Counters and partial sums fit the scratch array of mq_qlinear_noalloc
 // (32 MiB, ~16 us of traffic), so that entry point refuses no shape: larger
@@ -1382,8 +1391,8 @@ Choice choose(const QLinearArgs& p, bool can_split, const int64_t* Ns = nullptr,
                 return t.fixed_us + t.stage_us * (1.0 + t.busy * b * b) * (double)per;
             };
             const double exchange =
-                sp > 1 ? kSplitFixedUs + kSplitUsPerMB * (double)tiles * (2 * sp - 1) * t.tm *
-                                             t.tn * 4 * 1e-6
+                sp > 1 ? kSplitFixedUs + kSplitSliceUs * (sp - 1) +
+                             kSplitUsPerMB * (double)tiles * (2 * sp - 1) * t.tm * t.tn * 4 * 1e-6
                        : 0.0;
             const double tt = (double)full * round_us(1.0) + (rest ? round_us(busy) : 0.0) +
                               exchange;

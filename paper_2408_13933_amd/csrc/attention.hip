@@ -688,7 +688,7 @@ __global__ __launch_bounds__(256) void attn_sums_kernel(const int16_t* a, int64_
 __global__ __launch_bounds__(256) void transpose_i8_kernel(const int8_t* x, int64_t rows,
                                                            int64_t cols, int64_t ldx, int8_t* y)
 {
-    __shared__ int8_t t[64][68];  // t[c][r]
+    __shared__ __align__(4) int8_t t[64][68];  // t[c][r], read by dwords
     const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
     const int row = threadIdx.x >> 2, q = (threadIdx.x & 3) * 16;
     {

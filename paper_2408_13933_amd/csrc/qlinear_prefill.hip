@@ -282,7 +282,7 @@ __device__ __forceinline__ void prefill_epilogue(Acc& acc, Acc2& acc2, const Epi
     constexpr int32_t qmax = (1 << (C::OBITS - 1)) - 1;
     constexpr int OB = C::OBITS / 8;
     using S = Staging<C>;
-    static_assert(!STAGED || FAST, "staged stores assume whole 4-channel groups");
+    static_assert(!STAGED || FAST, "staged tiles requantize in the FAST form");
     constexpr int PASSES = STAGED ? S::PASSES : 1;
     constexpr int FNP = C::FN / PASSES;
     constexpr bool CASYM = ASYM && !C::A16;  // per-channel weight zero-points
